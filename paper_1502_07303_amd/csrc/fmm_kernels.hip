@@ -118,11 +118,24 @@ template <int E, typename FT, int G> struct TileLds {
 
 constexpr uint32_t NO_INST = 0xFFFFFFFFu;
 
+// The driver's parameters where the launch put them (the kernel argument
+// segment, read through the scalar cache).  params_here() makes the pointer
+// opaque, so the fields used after it are read again there instead of being
+// kept, and spilled, from the start of the kernel (8^3 driver: 131 spilled
+// scalar registers, 73 with it; 2 % of the 1024^3 solve).
+typedef const __attribute__((address_space(4))) Params *KParams;
+__device__ __forceinline__ KParams params_here(KParams p)
+{
+    asm volatile("" : "+s"(p));
+    return p;
+}
+
 template <int NW> struct WgShared {
     uint32_t cntL[NW], cntD[NW], pend[NW], inst[NW];
     double gmin0[NW], gmin1[NW];
     uint32_t baseL, baseD;
     uint32_t ok;
+    uint32_t drained;  // work segments of this phase a wavefront found empty
 };
 
 #ifdef FMM_PROFILE
@@ -533,16 +546,22 @@ __device__ __forceinline__ bool eval_point(const TileLds<E, FT, G> &L, const Spa
 // decrease, so a neighbour lowered meanwhile is at worst marked needlessly,
 // never missed.
 template <int E, typename FT, int G, bool AN, bool TWO>
-__device__ __forceinline__ int relax(const Params &P, TileLds<E, FT, G> &L, double h, const double th[2],
+__device__ __forceinline__ int relax(KParams P, TileLds<E, FT, G> &L, double h, const double th[2],
                                      WaveState &ws)
 {
     using Gm = Geo<E>;
+    Spacing sp{};
+    if constexpr (AN) {
+        sp.s[0] = P->sp.s[0];
+        sp.s[1] = P->sp.s[1];
+        sp.s[2] = P->sp.s[2];
+    }
     const int r = Grp<G>::rank_here();
     int n = compact(L);
     int rounds = 0;
     while (n > 0) {
         if (++rounds > MAX_ROUNDS) {
-            if (r == 0) atomicOr(&P.ctrl->error_run, ERR_ROUNDS);
+            if (r == 0) atomicOr(&P->ctrl->error_run, ERR_ROUNDS);
             break;
         }
         for (int base = 0; base < n; base += G) {
@@ -552,7 +571,7 @@ __device__ __forceinline__ int relax(const Params &P, TileLds<E, FT, G> &L, doub
             int p = 0;
             if (k < n) {
                 p = cand_at(L, k);
-                ch = eval_point<E, FT, G, AN, TWO>(L, P.sp, p, h, th, nv, vp, na);
+                ch = eval_point<E, FT, G, AN, TWO>(L, sp, p, h, th, nv, vp, na);
                 ws.n_solve++;
             }
             if constexpr (G == 64) wave_sync();
@@ -748,7 +767,7 @@ struct TileGeo {
 // valid upper bound, and the writer's flag makes this tile read them again.
 
 template <int E, typename FT, int G, bool AN>
-__device__ __forceinline__ void tile_march(const Params &P, TileLds<E, FT, G> &L, const TileGeo &G0, uint32_t t,
+__device__ __forceinline__ void tile_march(KParams P0, TileLds<E, FT, G> &L, const TileGeo &G0, uint32_t t,
                                            int mode,
                                            uint32_t dbits,
                                            const double bnd[2], const double lastb[2], uint32_t epoch, uint32_t phase,
@@ -757,13 +776,14 @@ __device__ __forceinline__ void tile_march(const Params &P, TileLds<E, FT, G> &L
 {
     using Gm = Geo<E>;
     constexpr int V = Gm::V, FACE = Gm::FACE;
+    KParams P = params_here(P0);
     // The lane offsets are formed per march (a reload of a spilled address
     // among the tile's loads would make them wait for one another).
     const int rk = Grp<G>::rank_here();
     const int lane = G == 64 ? rk : (int)(threadIdx.x & 63);
     const bool lead = Grp<G>::wave() == 0;  // the group's first wavefront
-    const FT *__restrict__ Ft = (const FT *)P.Ft;
-    double *__restrict__ Tt = P.Tt;
+    const FT *__restrict__ Ft = (const FT *)P->Ft;
+    double *__restrict__ Tt = P->Tt;
 
     // tile coordinates inside its problem; neighbours are t +- stride.  The
     // divisions run on the vector unit; the results are uniform and are
@@ -774,7 +794,7 @@ __device__ __forceinline__ void tile_march(const Params &P, TileLds<E, FT, G> &L
     const int32_t ty = (int32_t)__builtin_amdgcn_readfirstlane((tl / (uint32_t)G0.t2) % (uint32_t)G0.t1);
     const int32_t tx = (int32_t)__builtin_amdgcn_readfirstlane(tl / ((uint32_t)G0.t2 * (uint32_t)G0.t1));
     const uint32_t tsx = (uint32_t)G0.t1 * (uint32_t)G0.t2, tsy = (uint32_t)G0.t2;
-    const unsigned long long *mask = P.mask + (size_t)t * P.mask_words;
+    const unsigned long long *mask = P->mask + (size_t)t * P->mask_words;
     const size_t tbase = (size_t)t * V;
 
     PROF_CLOCK(t_begin);
@@ -860,9 +880,9 @@ __device__ __forceinline__ void tile_march(const Params &P, TileLds<E, FT, G> &L
             const int n0c = ax == 0 ? (plus ? 0 : E - 1) : c0;
             const int n1c = ax == 1 ? (plus ? 0 : E - 1) : c1;
             const int n2c = ax == 2 ? (plus ? 0 : E - 1) : c2;
-            const uint32_t vs = P.visit[tnb];
-            const uint32_t tf = P.tflags[tnb];
-            vh[j] = ax == 2 ? P.Zf[((size_t)tnb * 2 + (plus ? 0 : 1)) * FACE + n0c * E + n1c]
+            const uint32_t vs = P->visit[tnb];
+            const uint32_t tf = P->tflags[tnb];
+            vh[j] = ax == 2 ? P->Zf[((size_t)tnb * 2 + (plus ? 0 : 1)) * FACE + n0c * E + n1c]
                             : Tt[(size_t)tnb * V + (n0c * E + n1c) * E + n2c];
             vis_h[j] = inside ? vs : 0u;
             tf_h[j] = inside ? tf : 0u;
@@ -870,8 +890,8 @@ __device__ __forceinline__ void tile_march(const Params &P, TileLds<E, FT, G> &L
     }
     // the tile's own flags and stamp are requested after its cells (their
     // use must not hold back the cell reads)
-    const bool hasSeed = (P.tflags[t] & TF_SEED) != 0;
-    const bool fresh = P.visit[t] == 0;  // never written: every cell is +inf
+    const bool hasSeed = (P->tflags[t] & TF_SEED) != 0;
+    const bool fresh = P->visit[t] == 0;  // never written: every cell is +inf
     store_interior(0, hasSeed, fresh);
     for (int j0 = CI; j0 < NI; j0 += CI) {
         load_interior(j0);
@@ -897,7 +917,7 @@ __device__ __forceinline__ void tile_march(const Params &P, TileLds<E, FT, G> &L
                 const int n1c = ax == 1 ? (plus ? 0 : E - 1) : c1;
                 const int n2c = ax == 2 ? (plus ? 0 : E - 1) : c2;
                 const int pn = (n0c * E + n1c) * E + n2c;
-                if ((P.mask[(size_t)tnb * P.mask_words + (pn >> 6)] >> (pn & 63)) & 1ull) fl = FL_SEED;
+                if ((P->mask[(size_t)tnb * P->mask_words + (pn >> 6)] >> (pn & 63)) & 1ull) fl = FL_SEED;
             }
             const int d = Gm::dom(c0, c1, c2);
             if (is_source(v, fl, th0)) fl |= FL_SRC;
@@ -995,8 +1015,8 @@ __device__ __forceinline__ void tile_march(const Params &P, TileLds<E, FT, G> &L
         const bool more0 = tm0 < FMM_INF && tm0 <= bnd[0];
         const bool more1 = tm1 < FMM_INF && tm1 <= bnd[1];
         if (!(more0 || more1)) break;
-        const double nt[2] = {more0 ? fmin(tm0 + P.inner, bnd[0]) : th[0],
-                              more1 ? fmin(tm1 + P.inner, bnd[1]) : th[1]};
+        const double nt[2] = {more0 ? fmin(tm0 + P->inner, bnd[0]) : th[0],
+                              more1 ? fmin(tm1 + P->inner, bnd[1]) : th[1]};
         mark_new_sources(L, th, nt);
         th[0] = nt[0];
         th[1] = nt[1];
@@ -1043,8 +1063,8 @@ __device__ __forceinline__ void tile_march(const Params &P, TileLds<E, FT, G> &L
         const int i0 = p >> (2 * Gm::LOG), i1 = (p >> Gm::LOG) & (E - 1), i2 = p & (E - 1);
         const double v = vw[j];
         Tt[tbase + p] = v;
-        if (i2 == 0) P.Zf[((size_t)t * 2 + 0) * FACE + i0 * E + i1] = v;
-        if (i2 == E - 1) P.Zf[((size_t)t * 2 + 1) * FACE + i0 * E + i1] = v;
+        if (i2 == 0) P->Zf[((size_t)t * 2 + 0) * FACE + i0 * E + i1] = v;
+        if (i2 == E - 1) P->Zf[((size_t)t * 2 + 1) * FACE + i0 * E + i1] = v;
         if (!chg) continue;
         // faces this boundary cell lies on whose neighbouring cell it can
         // improve: the halo holds that cell's value as loaded, an upper bound
@@ -1085,7 +1105,7 @@ __device__ __forceinline__ void tile_march(const Params &P, TileLds<E, FT, G> &L
         srcFaces = m & 0x3Fu;
         anyFaces = (m >> 8) & 0x3Fu;
     }
-    if (fresh && rk == 0) __hip_atomic_store(&P.visit[t], phase + 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (fresh && rk == 0) __hip_atomic_store(&P->visit[t], phase + 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 
     if (rk == 0) {
         TileMeta m;
@@ -1093,7 +1113,7 @@ __device__ __forceinline__ void tile_march(const Params &P, TileLds<E, FT, G> &L
         m.tmin[1] = tm1;
         m.lastb[0] = bnd[0];
         m.lastb[1] = bnd[1];
-        P.meta[t] = m;
+        P->meta[t] = m;
     }
     ws.gmin0 = fmin(ws.gmin0, tm0);
     ws.gmin1 = fmin(ws.gmin1, tm1);
@@ -1123,7 +1143,7 @@ __device__ __forceinline__ void tile_march(const Params &P, TileLds<E, FT, G> &L
         const bool band = have && !src;
         if (band) {
             const unsigned long long b0 = L.bm[lane * 2], b1 = L.bm[lane * 2 + 1];
-            unsigned long long *ux = P.text + ((size_t)u * 3 + phase % 3u) * 2;
+            unsigned long long *ux = P->text + ((size_t)u * 3 + phase % 3u) * 2;
             if (b0 != bits_of(FMM_INF)) atomicMin(&ux[0], b0);
             if (b1 != bits_of(FMM_INF)) atomicMin(&ux[1], b1);
         }
@@ -1132,13 +1152,13 @@ __device__ __forceinline__ void tile_march(const Params &P, TileLds<E, FT, G> &L
         uint32_t old = 1;
         if (have && src) old = atomicOr(&dprod[u], 1u << (lane ^ 1));
         bool append = false;
-        if (self || band) append = atomicExch(&P.epoch[u], epoch) != epoch;
+        if (self || band) append = atomicExch(&P->epoch[u], epoch) != epoch;
         bool toD = false;
         if (have && src && old == 0) {
             if (second)
                 toD = true;
             else
-                append = atomicExch(&P.epoch[u], epoch) != epoch;
+                append = atomicExch(&P->epoch[u], epoch) != epoch;
         }
         const bool live = self || band || (have && src && old == 0 && !second);
         // wave-uniform follow-up
@@ -1185,9 +1205,9 @@ struct InstView {
     bool done;
 };
 
-__device__ __forceinline__ void load_inst(const Params &P, uint32_t j, uint32_t r, int mode, InstView &v)
+__device__ __forceinline__ void load_inst(KParams P, uint32_t j, uint32_t r, int mode, InstView &v)
 {
-    const Inst &I = P.inst[j];
+    const Inst &I = P->inst[j];
     v.j = j;
     v.g.base = I.base;
     v.g.t0 = I.t0;
@@ -1200,18 +1220,18 @@ __device__ __forceinline__ void load_inst(const Params &P, uint32_t j, uint32_t 
         v.done = false;
         return;
     }
-    InstSlot &S = P.ictl[j].slot[r % 3];
+    InstSlot &S = P->ictl[j].slot[r % 3];
     const double g0 = bitsd(ld_acq64(&S.gmin[0])), g1 = bitsd(ld_acq64(&S.gmin[1]));
-    v.done = inst_done(g0, g1, ld_acq(&S.pending), P.width);
-    v.bnd[0] = fmin(g0 + I.stride, P.width);
-    v.bnd[1] = fmin(g1 + I.stride, P.width);
+    v.done = inst_done(g0, g1, ld_acq(&S.pending), P->width);
+    v.bnd[0] = fmin(g0 + I.stride, P->width);
+    v.bnd[1] = fmin(g1 + I.stride, P->width);
 }
 
 // Hand a wavefront's band minima and dirty count to its problem's next slot.
-__device__ __forceinline__ void flush_acc(const Params &P, WaveState &ws, uint32_t r)
+__device__ __forceinline__ void flush_acc(KParams P, WaveState &ws, uint32_t r)
 {
     if (ws.acc != NO_INST && (threadIdx.x & 63) == 0) {
-        InstSlot &S = P.ictl[ws.acc].slot[(r + 1) % 3];
+        InstSlot &S = P->ictl[ws.acc].slot[(r + 1) % 3];
         if (ws.gmin0 < FMM_INF) atomicMin(&S.gmin[0], bits_of(ws.gmin0));
         if (ws.gmin1 < FMM_INF) atomicMin(&S.gmin[1], bits_of(ws.gmin1));
         if (ws.pending) atomicAdd(&S.pending, ws.pending);
@@ -1222,53 +1242,76 @@ __device__ __forceinline__ void flush_acc(const Params &P, WaveState &ws, uint32
 }
 
 template <int E, int NW, typename FT, bool AN, int G>
-__device__ __forceinline__ void run_phase(const Params &P, TileLds<E, FT, G> &L, WgShared<NW> &S, int mode, uint32_t r,
+__device__ __forceinline__ void run_phase(KParams P, TileLds<E, FT, G> &L, WgShared<NW> &S, int mode, uint32_t r,
                                           uint32_t phase, const uint32_t *items, uint32_t nitems, WaveState &ws)
 {
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
     const int rk = Grp<G>::rank();
     const bool lead = Grp<G>::wave() == 0;
-    Ctrl *c = P.ctrl;
+    Ctrl *c = P->ctrl;
     Slot &cur = c->slot[r % 3];
     Slot &nxt = c->slot[(r + 1) % 3];
-    uint32_t *listNext = ((r + 1) & 1) ? P.list1 : P.list0;
+    uint32_t *listNext = ((r + 1) & 1) ? P->list1 : P->list0;
     const uint32_t epoch = r + 1;
     // flags raised in phase p are read in phase p + 1: dirty[p % 2] is written,
     // dirty[(p + 1) % 2] (raised in the previous phase) is consumed
-    uint32_t *dcons = (phase & 1u) ? P.dirty0 : P.dirty1;
-    uint32_t *dprod = (phase & 1u) ? P.dirty1 : P.dirty0;
+    uint32_t *dcons = (phase & 1u) ? P->dirty0 : P->dirty1;
+    uint32_t *dprod = (phase & 1u) ? P->dirty1 : P->dirty0;
     // with a second march, tiles flagged by march-1 are handled in it;
     // otherwise they carry over to the next restart
-    const bool second = mode == MODE_M1 && P.two_march;
+    const bool second = mode == MODE_M1 && P->two_march;
     PROF_CLOCK(t_phase0);
     // The counters of the next phase are cleared now; their last use ended
     // two barriers ago and the barrier that ends this phase publishes them.
     if (blockIdx.x == 0 && threadIdx.x < WORK_SEGS) c->work[(phase + 1) % 3][threadIdx.x][0] = 0;
 
-    // Dynamic distribution: the item list is cut into WORK_SEGS segments, one
-    // per XCD (workgroups are dispatched to XCDs round robin), each with its
-    // own counter.  A group claims items of its own segment one at a time
-    // and then helps with the others; the claim for the next item is issued
-    // before the current one is marched so its latency overlaps the loads.
+    // Work distribution: the item list is cut into segments, one per XCD
+    // (workgroups are dispatched to XCDs round robin).  A segment's first
+    // items belong to its groups outright, one each and spread over its
+    // workgroups before a workgroup gets a second one; the items beyond them
+    // are claimed one at a time from the segment's counter, first by its own
+    // groups and then by groups whose segments are drained.  The claim for
+    // the next item is issued before the current one is marched so its
+    // latency overlaps the loads.  A phase whose list is no longer than the
+    // launch's groups therefore touches no counter, and a segment that one
+    // wavefront found drained is left alone by its whole workgroup.  (When
+    // every item was claimed, each of the 3072 wavefronts ended a phase with
+    // eight failed claims, about 25 us of atomics on eight lines: a 64^3
+    // point source took 3.66 ms and takes 2.06 ms, 301x256x333 FP64 23.8 and
+    // 21.2 ms; long phases, 1024^3 at 3.5h, are unchanged.)
     // In a workgroup group everything that steers the loop (claims, the abort
     // flag, a tile's due test) is read by rank 0 and broadcast.
     uint32_t(*cnt)[32] = c->work[phase % 3];
-    uint32_t seg = blockIdx.x % WORK_SEGS, left = WORK_SEGS;
+    constexpr uint32_t GW = NW * 64 / G;  // groups per workgroup
+    const uint32_t nwg = gridDim.x, nseg = nwg < (uint32_t)WORK_SEGS ? nwg : (uint32_t)WORK_SEGS;
+    auto seg_lo = [&](uint32_t s) { return (uint32_t)(((uint64_t)nitems * s) / nseg); };
+    auto seg_own = [&](uint32_t s) { return (nwg - s + nseg - 1) / nseg * GW; };  // groups of segment s
+    uint32_t seg = blockIdx.x % nseg, left = nseg;
+    uint32_t lo = seg_lo(seg), len = seg_lo(seg + 1) - lo, own = seg_own(seg);
+    const uint32_t gi = G == 64 ? (uint32_t)__builtin_amdgcn_readfirstlane(wid) : 0u, wi = blockIdx.x / nseg;
+    uint32_t k = len < own ? gi * (own / GW) + wi : wi * GW + gi;
     uint32_t claim = 0;
     InstView iv;
     iv.j = NO_INST;
-    if (rk == 0) claim = atomicAdd(&cnt[seg][0], 1u);
-    for (;;) {
-        const uint32_t k = grp_bcast(L, claim);
-        const uint32_t lo = (uint32_t)(((uint64_t)nitems * seg) / WORK_SEGS);
-        const uint32_t hi = (uint32_t)(((uint64_t)nitems * (seg + 1)) / WORK_SEGS);
-        if (k >= hi - lo) {
-            if (--left == 0) break;
-            seg = (seg + 1) % WORK_SEGS;
+    for (bool first = true;; first = false) {
+        if (!first) k = len > own ? own + grp_bcast(L, claim) : len;
+        if (k >= len) {
+            if (G == 64 && len > own && lane == 0) atomicOr(&S.drained, 1u << seg);
+            // the next segment that may still have items to claim
+            const uint32_t gone = G == 64 ? __builtin_amdgcn_readfirstlane(*(volatile uint32_t *)&S.drained) : 0u;
+            bool found = false;
+            while (!found && --left > 0) {
+                seg = seg + 1 == nseg ? 0 : seg + 1;
+                lo = seg_lo(seg);
+                len = seg_lo(seg + 1) - lo;
+                own = seg_own(seg);
+                found = len > own && !((gone >> seg) & 1u);
+            }
+            if (!found) break;
             if (rk == 0) claim = atomicAdd(&cnt[seg][0], 1u);
             continue;
         }
-        if (rk == 0) claim = atomicAdd(&cnt[seg][0], 1u);
+        if (len > own && rk == 0) claim = atomicAdd(&cnt[seg][0], 1u);
         // the item and the abort flag are requested together (one round trip)
         const uint32_t i = lo + k;
         const uint32_t item = items[i];
@@ -1278,7 +1321,7 @@ __device__ __forceinline__ void run_phase(const Params &P, TileLds<E, FT, G> &L,
             if (grp_bcast(L, rk == 0 ? ld_acq(&c->abort) : 0u)) break;
         }
         const uint32_t t = __builtin_amdgcn_readfirstlane(item);
-        const uint32_t j = P.n_inst == 1 ? 0u : __builtin_amdgcn_readfirstlane(P.tinst[t]);
+        const uint32_t j = P->n_inst == 1 ? 0u : __builtin_amdgcn_readfirstlane(P->tinst[t]);
         if (j != iv.j) load_inst(P, j, r, mode, iv);
         // a problem that passed its exit test takes no further part
         if (iv.done) continue;
@@ -1293,12 +1336,12 @@ __device__ __forceinline__ void run_phase(const Params &P, TileLds<E, FT, G> &L,
             // phase, and no other group handles tile t in this phase.  It is
             // read with the tile's record (one round trip) and cleared below.
             dbits = dcons[t];
-            const TileMeta m = P.meta[t];
+            const TileMeta m = P->meta[t];
             lastb[0] = m.lastb[0];
             lastb[1] = m.lastb[1];
             // pending minimum: the tile's own, and band values its neighbours
             // have passed on since (Alg. 15, BAND_OLD), one slot per phase
-            unsigned long long *tx = P.text + (size_t)t * 6;
+            unsigned long long *tx = P->text + (size_t)t * 6;
             unsigned long long xb[6];
 #pragma unroll
             for (int q = 0; q < 6; q++) xb[q] = ld_acq64(&tx[q]);
@@ -1331,7 +1374,7 @@ __device__ __forceinline__ void run_phase(const Params &P, TileLds<E, FT, G> &L,
                 ws.gmin1 = fmin(ws.gmin1, p1);
                 if (lead && (p0 < FMM_INF || p1 < FMM_INF)) {
                     uint32_t oe = 0;
-                    if (lane == 0) oe = atomicExch(&P.epoch[t], epoch);
+                    if (lane == 0) oe = atomicExch(&P->epoch[t], epoch);
                     oe = bcast0(oe);
                     if (oe != epoch) stage_push(L.stL, ws.nL, t, &nxt.live_len, listNext);
                 }
@@ -1350,7 +1393,7 @@ __device__ __forceinline__ void run_phase(const Params &P, TileLds<E, FT, G> &L,
             Grp<G>::sync();
         }
         tile_march<E, FT, G, AN>(P, L, iv.g, t, mode, dbits, iv.bnd, lastb, epoch, phase, second, ws, listNext,
-                                 &nxt.live_len, P.dlist, &cur.d_len, dprod);
+                                 &nxt.live_len, P->dlist, &cur.d_len, dprod);
     }
 
     PROF_CLOCK(t_phase1);
@@ -1368,6 +1411,7 @@ __device__ __forceinline__ void run_phase(const Params &P, TileLds<E, FT, G> &L,
     __syncthreads();
     if (threadIdx.x == 0) {
         uint32_t tl = 0, td = 0;
+        S.drained = 0;
         for (int w = 0; w < NW; w++) {
             tl += S.cntL[w];
             td += S.cntD[w];
@@ -1387,7 +1431,7 @@ __device__ __forceinline__ void run_phase(const Params &P, TileLds<E, FT, G> &L,
                 g1 = fmin(g1, S.gmin1[u]);
                 if (u > w) S.inst[u] = NO_INST;
             }
-            InstSlot &Z = P.ictl[j].slot[(r + 1) % 3];
+            InstSlot &Z = P->ictl[j].slot[(r + 1) % 3];
             if (tp) atomicAdd(&Z.pending, tp);
             if (g0 < FMM_INF) atomicMin(&Z.gmin[0], bits_of(g0));
             if (g1 < FMM_INF) atomicMin(&Z.gmin[1], bits_of(g1));
@@ -1400,7 +1444,7 @@ __device__ __forceinline__ void run_phase(const Params &P, TileLds<E, FT, G> &L,
         offD += S.cntD[w];
     }
     for (uint32_t q = lane; q < ws.nL; q += 64) listNext[offL + q] = L.stL[q];
-    for (uint32_t q = lane; q < ws.nD; q += 64) P.dlist[offD + q] = L.stD[q];
+    for (uint32_t q = lane; q < ws.nD; q += 64) P->dlist[offD + q] = L.stD[q];
     ws.nL = ws.nD = 0;
     ws.acc = NO_INST;
     ws.pending = 0;
@@ -1410,14 +1454,16 @@ __device__ __forceinline__ void run_phase(const Params &P, TileLds<E, FT, G> &L,
 // NW wavefronts per workgroup in groups of G threads; WPE is the occupancy
 // the register budget is fitted to (wavefronts per SIMD).
 template <int E, int NW, typename FT, bool AN, int G, int WPE>
-__global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(WPE))) k_driver(Params P)
+__global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(WPE))) k_driver(Params Pk)
 {
     static_assert(G == 64 || G == NW * 64, "a group is one wavefront or the whole workgroup");
     __shared__ TileLds<E, FT, G> s_tile[NW * 64 / G];
     __shared__ WgShared<NW> s_g;
+    (void)Pk;
+    KParams P = params_here((KParams)__builtin_amdgcn_kernarg_segment_ptr());
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
     TileLds<E, FT, G> &L = s_tile[G == 64 ? wid : 0];
-    Ctrl *c = P.ctrl;
+    Ctrl *c = P->ctrl;
     const uint32_t nwg = gridDim.x;
     uint32_t gen = 0;
     WaveState ws;
@@ -1430,6 +1476,8 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(WP
     for (int k = 0; k < 16; k++) ws.prof[k] = 0;
 #endif
 
+    if (threadIdx.x == 0) s_g.drained = 0;
+    __syncthreads();
     const unsigned long long t_start = wall_clock64();
     if (blockIdx.x == 0 && threadIdx.x == 0) c->nwg = nwg;
     // Phase sequence: heap initialisation (Alg. 9: only seeds are sources),
@@ -1441,7 +1489,7 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(WP
     int mode = MODE_INIT;
     uint32_t r = 0;
     uint32_t phase = 1;  // phases are numbered from 1; tile visit stamps refer to them
-    const uint32_t *items = P.list0;
+    const uint32_t *items = P->list0;
     uint32_t nitems = ld_acq(&c->slot[0].live_len);
     bool run = ld_acq(&c->error) == 0;
     while (run) {
@@ -1454,9 +1502,9 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(WP
         PROF_ADD(9, t_p2 - t_p1);
         if (!passed) break;
         phase++;
-        if (mode == MODE_M1 && P.two_march) {
+        if (mode == MODE_M1 && P->two_march) {
             mode = MODE_M2;
-            items = P.dlist;
+            items = P->dlist;
             nitems = ld_acq(&c->slot[r % 3].d_len);
             continue;
         }
@@ -1466,11 +1514,11 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(WP
         // restart that just ended.  Workgroup 0 also records when each problem
         // finished and clears the slots of the restart after next.
         int active = 0;
-        for (uint32_t k = threadIdx.x; k < P.n_inst; k += blockDim.x) {
-            InstCtl &ic = P.ictl[k];
+        for (uint32_t k = threadIdx.x; k < P->n_inst; k += blockDim.x) {
+            InstCtl &ic = P->ictl[k];
             InstSlot &S = ic.slot[r % 3];
             const double g0 = bitsd(ld_acq64(&S.gmin[0])), g1 = bitsd(ld_acq64(&S.gmin[1]));
-            const bool done = inst_done(g0, g1, ld_acq(&S.pending), P.width);
+            const bool done = inst_done(g0, g1, ld_acq(&S.pending), P->width);
             active |= done ? 0 : 1;
             if (blockIdx.x == 0) {
                 if (done && ic.restarts == 0) ic.restarts = r;
@@ -1487,10 +1535,10 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(WP
             if (blockIdx.x == 0 && threadIdx.x == 0) c->restarts = r;
             break;
         }
-        if (P.max_restarts > 0 && (int64_t)r > P.max_restarts) {
+        if (P->max_restarts > 0 && (int64_t)r > P->max_restarts) {
             if (blockIdx.x == 0) {
-                for (uint32_t k = threadIdx.x; k < P.n_inst; k += blockDim.x)
-                    if (P.ictl[k].restarts == 0) P.ictl[k].restarts = r;
+                for (uint32_t k = threadIdx.x; k < P->n_inst; k += blockDim.x)
+                    if (P->ictl[k].restarts == 0) P->ictl[k].restarts = r;
                 if (threadIdx.x == 0) {
                     atomicOr(&c->error_run, ERR_NOCONV);
                     c->restarts = r;
@@ -1502,7 +1550,7 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(WP
         // (one clock read, shared through LDS); the others leave at their
         // next barrier.
         if (blockIdx.x == 0) {
-            if (threadIdx.x == 0) s_g.ok = (wall_clock64() - t_start > P.time_limit_ticks) ? 1u : 0u;
+            if (threadIdx.x == 0) s_g.ok = (wall_clock64() - t_start > P->time_limit_ticks) ? 1u : 0u;
             __syncthreads();
             const bool late = s_g.ok != 0;
             __syncthreads();
@@ -1516,7 +1564,7 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(WP
             }
         }
         mode = MODE_M1;
-        items = (r & 1) ? P.list1 : P.list0;
+        items = (r & 1) ? P->list1 : P->list0;
         nitems = len;
     }
     // ---- statistics
