@@ -14,7 +14,9 @@ namespace fmm {
 // row-major (n0, n1, n2).
 struct AdjInst {
     int64_t n0, n1, n2;
-    int64_t base;  // global index of the problem's first point in the workspace arrays
+    int64_t base;  // global index of the problem's first point in the level sweep's arrays
+    int32_t t0, t1, t2;  // 8^3 tiles per axis (tile sweep)
+    uint32_t tbase;      // global index of the problem's first tile (tile sweep)
     double h;
     const void *F;
     const double *T;
@@ -37,6 +39,9 @@ struct AdjCtrl {
     uint32_t magic;                   // ADJ_MAGIC once a run has initialised the workspace
     alignas(128) unsigned long long len[3];  // frontier lengths, by level mod 3
     alignas(128) unsigned long long n_points;  // points of the linear system
+    // tile sweep: claim counters of the phases (by phase mod 3), one per
+    // segment of the work list and 128 B apart
+    alignas(128) uint32_t work[3][8][32];
 };
 
 struct AdjParams {
@@ -47,6 +52,32 @@ struct AdjParams {
     uint8_t *code;    // per point: upwind set, 2 bits per axis
     uint64_t *list0, *list1;  // frontiers
 };
+
+// The tile sweep's state: per 8^3 tile, 64 rows (x, y) of 8 cells along axis 2.
+// A row word holds, one bit per cell: bytes 0 to 5 the cells whose upwind
+// neighbour on axis 0, 1, 2 is the minus (even bytes) or plus (odd bytes) one,
+// byte 6 the cells that are solved and byte 7 the cells of the linear system.
+struct AdjTileParams {
+    AdjCtrl *ctrl;
+    const AdjInst *inst;
+    uint32_t n_inst, ntiles;
+    // 16 words per tile: tile strides along axes 0 and 1, flags (bits 0 to 5:
+    // there is a tile across face f; bit 6: per-axis spacing), problem, and per
+    // face 64 bits for the cells that wait for a contribution across it
+    uint32_t *head;
+    uint64_t *row;    // 64 row words per tile
+    double *u;        // |T|
+    double *c;        // sign(T) dL/dT until the cell is solved, then lambda = lt / S
+    uint32_t *lev;    // dependency level of a solved cell (1: no dependents)
+    // per tile and face (2 * axis + 1 for the + side), 64 cells of the face:
+    double *fw;    // weighted difference to the upwind neighbour across the face (0: none)
+    uint64_t *fo;  // contribution passed across it (ADJT_WAIT until the cell is solved, 0 bits: none)
+    uint32_t *fl;  // the cell's level (ADJT_NOLEV until it is solved, 0: none)
+    uint32_t *tag;           // last phase the tile was listed for
+    uint32_t *list0, *list1;  // tiles of the current and the next phase
+};
+constexpr uint64_t ADJT_WAIT = ~0ull;
+constexpr uint32_t ADJT_NOLEV = ~0u;
 
 constexpr int ADJ_PACK = 16;
 struct AdjPack {
@@ -61,6 +92,17 @@ struct AdjGather {
     double *out;
     int64_t n;
     int64_t base[ADJ_GATHER];
+    uint32_t m, accumulate;
+};
+
+// The same for the tile sweep, by the problems' first tiles.
+struct AdjTileGather {
+    double *out;
+    int64_t n0, n1, n2;
+    int32_t t0, t1, t2;
+    uint32_t tbase[ADJ_GATHER];
+    const void *F[ADJ_GATHER];
+    double h[ADJ_GATHER];
     uint32_t m, accumulate;
 };
 
@@ -93,6 +135,39 @@ inline AdjLayout adj_layout(int64_t n, uint64_t total)
     return L;
 }
 
+// The same for the tile sweep over nt tiles (36 bytes per cell of a tile).
+struct AdjTileLayout {
+    size_t off_ctrl, off_inst, off_head, off_row, off_u, off_c, off_lev, off_fw, off_fo, off_fl, off_tag, off_list0,
+        off_list1, total;
+};
+
+inline AdjTileLayout adj_tile_layout(int64_t n, uint64_t nt)
+{
+    AdjTileLayout L;
+    size_t o = 0;
+    auto take = [&](size_t bytes) {
+        const size_t at = o;
+        o = adj_align(o + bytes);
+        return at;
+    };
+    L.off_ctrl = take(sizeof(AdjCtrl));
+    L.off_inst = take(sizeof(AdjInst) * (size_t)n);
+    L.off_head = take(64 * nt);
+    L.off_row = take(8 * 64 * nt);
+    L.off_u = take(8 * 512 * nt);
+    L.off_c = take(8 * 512 * nt);
+    L.off_lev = take(4 * 512 * nt);
+    L.off_fw = take(8 * 384 * nt);
+    L.off_fo = take(8 * 384 * nt);
+    L.off_fl = take(4 * 384 * nt);
+    L.off_tag = take(4 * nt);
+    L.off_list0 = take(4 * nt);
+    L.off_list1 = take(4 * nt);
+    L.total = o;
+    return L;
+}
+
+hipError_t launch_adjoint_tiles(const AdjTileParams &P, const AdjInst *insts, int64_t n, bool f64, hipStream_t s);
 hipError_t launch_adjoint(const AdjParams &P, const AdjInst *insts, int64_t n, bool f64, hipStream_t s);
 
 }  // namespace fmm

@@ -505,10 +505,34 @@ static bool adj_problem_ok(const fmm_adjoint_problem &q)
     return q.F && q.T && q.status && q.dL_dT && q.dL_dF;
 }
 
-static uint64_t adj_total(int64_t n, const fmm_adjoint_problem *q, std::vector<AdjInst> *insts)
+// The tile sweep takes batches whose problems have at least 8 points along
+// every axis.  A thinner grid fills its 8^3 tiles to an eighth or less (up to
+// 288 bytes of workspace per point of a plane, against the level sweep's 29),
+// so batches with such a problem keep the level sweep.  It numbers tiles with 32
+// bits: larger batches, too.
+static bool adj_tiled(int64_t n, const fmm_adjoint_problem *q)
 {
-    uint64_t total = 0;
+    uint64_t nt = 0;
     for (int64_t i = 0; i < n; i++) {
+        if (q[i].n0 < 8 || q[i].n1 < 8 || q[i].n2 < 8) return false;
+        int32_t t[3];
+        uint64_t k = 0;
+        if (!tile_grid(q[i].n0, q[i].n1, q[i].n2, 8, t, &k)) return false;
+        nt += k;
+        if (nt >= 0xFFFFFFF0ull) return false;
+    }
+    return true;
+}
+
+// Points and 8^3 tiles of a batch; its problem descriptors (nullable).
+static void adj_sizes(int64_t n, const fmm_adjoint_problem *q, std::vector<AdjInst> *insts, uint64_t *points,
+                      uint64_t *tiles)
+{
+    uint64_t total = 0, nt = 0;
+    for (int64_t i = 0; i < n; i++) {
+        int32_t t[3] = {0, 0, 0};
+        uint64_t k = 0;
+        tile_grid(q[i].n0, q[i].n1, q[i].n2, 8, t, &k);
         if (insts) {
             AdjInst &I = (*insts)[(size_t)i];
             memset(&I, 0, sizeof I);
@@ -516,6 +540,10 @@ static uint64_t adj_total(int64_t n, const fmm_adjoint_problem *q, std::vector<A
             I.n1 = q[i].n1;
             I.n2 = q[i].n2;
             I.base = (int64_t)total;
+            I.t0 = t[0];
+            I.t1 = t[1];
+            I.t2 = t[2];
+            I.tbase = (uint32_t)nt;
             I.h = q[i].h;
             I.F = q[i].F;
             I.T = q[i].T;
@@ -525,8 +553,10 @@ static uint64_t adj_total(int64_t n, const fmm_adjoint_problem *q, std::vector<A
             I.sp = spacing_of(q[i].axis_scale);
         }
         total += (uint64_t)(q[i].n0 * q[i].n1 * q[i].n2);
+        nt += k;
     }
-    return total;
+    *points = total;
+    *tiles = nt;
 }
 
 size_t fmm_adjoint_workspace_bytes(int64_t n_problems, const fmm_adjoint_problem *problems)
@@ -537,7 +567,10 @@ size_t fmm_adjoint_workspace_bytes(int64_t n_problems, const fmm_adjoint_problem
         uint64_t nt;
         if (!tile_grid(problems[i].n0, problems[i].n1, problems[i].n2, 4, t, &nt)) return 0;
     }
-    return adj_layout(n_problems, adj_total(n_problems, problems, nullptr)).total;
+    uint64_t total = 0, nt = 0;
+    adj_sizes(n_problems, problems, nullptr, &total, &nt);
+    return adj_tiled(n_problems, problems) ? adj_tile_layout(n_problems, nt).total
+                                           : adj_layout(n_problems, total).total;
 }
 
 int fmm_adjoint_batch(int64_t n_problems, const fmm_adjoint_problem *problems, fmm_dtype F_dtype,
@@ -556,8 +589,33 @@ int fmm_adjoint_batch(int64_t n_problems, const fmm_adjoint_problem *problems, f
         if (a.n0 != b.n0 || a.n1 != b.n1 || a.n2 != b.n2) return FMM_EINVAL;
     }
     std::vector<AdjInst> insts((size_t)n_problems);
-    const uint64_t total = adj_total(n_problems, problems, &insts);
+    uint64_t total = 0, nt = 0;
+    adj_sizes(n_problems, problems, &insts, &total, &nt);
     if (total >= (1ull << 40)) return FMM_EINVAL;
+    if (adj_tiled(n_problems, problems)) {
+        const AdjTileLayout L = adj_tile_layout(n_problems, nt);
+        if (workspace_bytes < L.total) return FMM_ENOMEM;
+        char *b = (char *)workspace;
+        AdjTileParams P;
+        P.ctrl = (AdjCtrl *)(b + L.off_ctrl);
+        P.inst = (const AdjInst *)(b + L.off_inst);
+        P.n_inst = (uint32_t)n_problems;
+        P.ntiles = (uint32_t)nt;
+        P.head = (uint32_t *)(b + L.off_head);
+        P.row = (uint64_t *)(b + L.off_row);
+        P.u = (double *)(b + L.off_u);
+        P.c = (double *)(b + L.off_c);
+        P.lev = (uint32_t *)(b + L.off_lev);
+        P.fw = (double *)(b + L.off_fw);
+        P.fo = (uint64_t *)(b + L.off_fo);
+        P.fl = (uint32_t *)(b + L.off_fl);
+        P.tag = (uint32_t *)(b + L.off_tag);
+        P.list0 = (uint32_t *)(b + L.off_list0);
+        P.list1 = (uint32_t *)(b + L.off_list1);
+        return launch_adjoint_tiles(P, insts.data(), n_problems, F_dtype == FMM_F64, (hipStream_t)stream) == hipSuccess
+                   ? FMM_OK
+                   : FMM_EHIP;
+    }
     const AdjLayout L = adj_layout(n_problems, total);
     if (workspace_bytes < L.total) return FMM_ENOMEM;
     char *b = (char *)workspace;
