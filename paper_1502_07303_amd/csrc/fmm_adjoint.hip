@@ -1074,7 +1074,10 @@ template <bool AN> static hipError_t launch_sweep(const AdjTileParams &P, hipStr
     if (occ <= 0) return hipErrorInvalidConfiguration;
     AdjTileParams Pc = P;
     void *args[] = {&Pc};
-    return launch_coresident((const void *)kern, dim3((unsigned)adj_cus()), dim3(ADJT_NW * 64), args, s);
+    // a workgroup per CU, fewer if there are not eight tiles for each (as in
+    // the forward driver: the barrier is cheaper)
+    const unsigned grid = std::min((unsigned)adj_cus(), (P.ntiles + 7u) / 8u);
+    return launch_coresident((const void *)kern, dim3(grid), dim3(ADJT_NW * 64), args, s);
 }
 
 template <typename FT> static hipError_t launch_adjoint_tiles_t(const AdjTileParams &P, const AdjInst *insts, int64_t n,
