@@ -23,7 +23,7 @@ namespace fmm {
 // library routine on a branch that the solver's discriminants practically
 // never reach; +inf (only when r = +inf, where the solver returns +inf from
 // its first root) gives NaN, which the root comparisons reject.
-__device__ __forceinline__ double solver_sqrt(double x)
+__device__ __forceinline__ double solver_sqrt_normal(double x)
 {
     const double y = __builtin_amdgcn_rsq(x);
     double s = x * y, h = y * 0.5;
@@ -33,7 +33,12 @@ __device__ __forceinline__ double solver_sqrt(double x)
     double d = __builtin_fma(-s, s, x);
     s = __builtin_fma(d, h, s);
     d = __builtin_fma(-s, s, x);
-    s = __builtin_fma(d, h, s);
+    return __builtin_fma(d, h, s);
+}
+
+__device__ __forceinline__ double solver_sqrt(double x)
+{
+    double s = solver_sqrt_normal(x);
     if (__builtin_expect(x < 0x1p-767, 0)) {
         asm volatile("");  // keeps the rare path a branch (not computed and selected)
         s = sqrt(x);
@@ -112,10 +117,43 @@ __device__ __forceinline__ double godunov_sel(double x, double y, double z, doub
     return best;
 }
 
+// The same root with one square root.  In exact arithmetic the candidate of k
+// values is causal iff the sum of (a_k - a_i)^2 over them is below r^2, and
+// more values give a smaller root, so the sums decide which root to form.
+// Rounding can decide otherwise only where a sum is close to r^2: the two roots
+// then differ by about (u - a)^2 / (4 r), which exceeds a few ulps of the values
+// once |r^2 - sum| > r^2 2^-22 sqrt(a1 / r), and t bounds twice that without a
+// root.  Closer calls, and r^2 near the ends of the exponent range (r = +inf
+// too), take godunov_sel(): bitwise the same result everywhere (checked on the
+// host on 4e8 triples, most of them around the decisions).  NaN sums, from
+// absent values, compare false and leave the first root.
 __device__ __forceinline__ double godunov(double x, double y, double z, double r)
 {
-    int k;
-    return godunov_sel(x, y, z, r, &k);
+    const double lo = fmin(x, y), hi = fmax(x, y);
+    const double a3 = fmax(hi, z), m = fmin(hi, z);
+    const double a1 = fmin(lo, m), a2 = fmax(lo, m);
+    const double r2 = r * r;
+    const double d12 = a2 - a1, d13 = a3 - a1, d23 = a3 - a2;
+    const double q12 = d12 * d12, q13 = d13 * d13, q23 = d23 * d23;
+    const double f3 = q13 + q23;
+    const double t = __builtin_fma(r2, 0x1p-16, (r * fabs(a1)) * 0x1p-28);
+    const uint32_t e = (uint32_t)((unsigned long long)__double_as_longlong(r2) >> 52);  // r2 >= 0
+    const bool three = f3 < r2, two = q12 < r2;
+    // selects and a single test (the lanes differ: no branch is saved)
+    const double D2 = 2.0 * r2 - q12, D3 = 3.0 * r2 - ((q12 + q13) + q23);
+    const double D = __builtin_unpredictable(three) ? D3 : D2;
+    const double s12 = a1 + a2, s123 = s12 + a3;
+    const double v = (__builtin_unpredictable(three) ? s123 : s12) + solver_sqrt_normal(D);
+    const double v3 = div3(v), v2 = v * 0.5;
+    const double root = __builtin_unpredictable(three) ? v3 : v2, u1 = a1 + r;
+    double best = __builtin_unpredictable(two) ? root : u1;
+    const int close = (int)(fabs(r2 - q12) <= t) | (int)(fabs(r2 - f3) <= t) | (int)(e - (1023u - 760u) > 760u + 990u);
+    if (__builtin_expect(close, 0)) {
+        asm volatile("");  // a branch, not computed and selected
+        int k;
+        best = godunov_sel(x, y, z, r, &k);
+    }
+    return best;
 }
 
 // The local solver with per-axis spacing h s_i (weights w_i = 1 / s_i^2):

@@ -432,17 +432,16 @@ __device__ __forceinline__ bool is_source(double v, uint8_t fl, const double bnd
     return a <= (v < 0.0 ? bnd[0] : bnd[1]);
 }
 
-// r = h / F of interior point p (+inf for seeds and impassable cells).
+// r = h / F of interior point p.  Fixed cells (seeds, impassable cells) hold
+// speed 0, whose r is NaN, or the r = +inf of an FP64 slot: no root from either
+// beats a value.
 template <int E, typename FT, int G>
 __device__ __forceinline__ double cell_r(const TileLds<E, FT, G> &L, int p, double h)
 {
-    if constexpr (sizeof(FT) == 8) {
+    if constexpr (sizeof(FT) == 8)
         return L.F[p];
-    } else {
-        // fixed cells (seeds, impassable cells) hold speed 0
-        const float f = L.F[p];
-        return f > 0.0f ? solver_div(h, (double)f) : FMM_INF;
-    }
+    else
+        return solver_div(h, (double)L.F[p]);
 }
 
 // Evaluate Solve_Quadratic_Parallel at interior point p: returns true and the
@@ -483,7 +482,7 @@ __device__ __forceinline__ bool eval_point(const TileLds<E, FT, G> &L, const Spa
         // no finite neighbour: the solver returns +inf, which never beats vp
         int kk;
         const double u = AN ? godunov_w_sel(m[0], m[1], m[2], sp.s[0], sp.s[1], sp.s[2], r, &kk)
-                            : godunov_sel(m[0], m[1], m[2], r, &kk);
+                            : godunov(m[0], m[1], m[2], r);
         out = u;
         return u < vp;
     }
