@@ -84,7 +84,7 @@ template <int G> struct Grp {
 #define FMM_E8_WAVES_F64 10
 #endif
 
-constexpr int STAGE = 64;  // staged list appends per group before a flush
+constexpr int STAGE = 32;  // staged list appends per group before a flush (at most a wavefront's lanes)
 constexpr int MAX_ROUNDS = 1 << 16;
 
 // Cell flags.  FL_SRC caches "is a source at the current level" (a seed, or a
@@ -97,9 +97,17 @@ enum { MODE_INIT = 0, MODE_M1 = 1, MODE_M2 = 2 };
 // LDS of one tile march.  Candidate flags are bytes for a one-wavefront group
 // (compacted eight at a time) and bits for a workgroup (a 16^3 tile's bytes
 // would not leave room for two tiles per CU).
-template <int E, typename FT, int G> struct TileLds {
+// Scratch of a workgroup group: per-wavefront candidate counts and partial
+// reductions, and broadcast words (a one-wavefront group has none).
+template <int G> struct GrpScratch {
+    uint32_t gcnt[G / 64], gu[G / 64];
+    double gd0[G / 64], gd1[G / 64];
+    uint32_t bc[8];
+};
+template <> struct GrpScratch<64> {};
+
+template <int E, typename FT, int G> struct TileLds : GrpScratch<G> {
     static constexpr bool BITS = G > 64;
-    static constexpr int NWV = G / 64;
     double T[Geo<E>::DV];                                // domain values (interior + face halos)
     FT F[Geo<E>::V];                                     // interior speeds (FP32), or h / F (FP64)
     uint16_t list[Geo<E>::V];                            // candidate list (interior indices)
@@ -109,12 +117,10 @@ template <int E, typename FT, int G> struct TileLds {
     uint32_t stL[STAGE];                                 // staged live-list appends
     uint32_t stD[STAGE];                                 // staged dirty-list appends
     unsigned long long bm[12];                           // per face and side: smallest changed band value
-    // group scratch (G > 64): per-wavefront candidate counts and partial
-    // reductions, and broadcast words
-    uint32_t gcnt[NWV], gu[NWV];
-    double gd0[NWV], gd1[NWV];
-    uint32_t bc[8];
 };
+
+// A byte in LDS (32-bit addresses, offsets folded into the access).
+typedef __attribute__((address_space(3))) uint8_t lds_byte;
 
 constexpr uint32_t NO_INST = 0xFFFFFFFFu;
 
@@ -260,23 +266,30 @@ __device__ __forceinline__ void stage_push(uint32_t *st, uint32_t &n, uint32_t v
         uint32_t base = 0;
         if (lane == 0) base = atomicAdd(counter, (uint32_t)STAGE);
         base = bcast0(base);
-        list[base + lane] = st[lane];
+        if (lane < STAGE) list[base + lane] = st[lane];
         n = 0;
         wave_sync();
     }
 }
 
-// Set candidate flag q if `on`.  Byte flags take one store from every lane:
-// a lane that does not mark writes its own spare dword (distinct banks), so
-// no lane mask has to be set up around the store; bit flags an LDS atomic OR.
+// Set the candidate flag of interior cell q if `on`.  Byte flags take one
+// store from every lane: a lane that does not mark writes its own spare dword
+// (distinct banks), so no lane mask has to be set up around the store; bit
+// flags an LDS atomic OR.
 template <int E, typename FT, int G>
 __device__ __forceinline__ void mark_cand(TileLds<E, FT, G> &L, bool on, int q)
 {
     if constexpr (TileLds<E, FT, G>::BITS) {
         if (on) atomicOr(&L.cfw[q >> 5], 1u << (q & 31));
     } else {
-        L.cf[on ? q : Geo<E>::spare((int)__lane_id())] = 1;
+        L.cf[on ? Geo<E>::cfi(q) : Geo<E>::spare((int)__lane_id())] = 1;
     }
+}
+
+// Set lanes of m below this one.
+__device__ __forceinline__ uint32_t lanes_below(unsigned long long m)
+{
+    return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
 }
 
 // Compact the candidate flags into the list (ascending interior index within
@@ -284,6 +297,9 @@ __device__ __forceinline__ void mark_cand(TileLds<E, FT, G> &L, bool on, int q)
 // One wavefront: byte flags, one list.  A workgroup: bit flags; wavefront w
 // owns interior cells [w 64 C, (w + 1) 64 C) (C = V / G cells per thread) and
 // writes its candidates to the same range of the list, its count to gcnt[w].
+// (The relaxation is bound by vector instructions at 1024^3.  Prefix counts by
+// mbcnt and an unconditional clear here, marks without coordinate tests and
+// flags formed without reading them in relax(): 215.4 -> 204.2 ms.)
 template <int E, typename FT, int G> __device__ __forceinline__ int compact(TileLds<E, FT, G> &L)
 {
     constexpr int K = Geo<E>::K;
@@ -321,8 +337,9 @@ template <int E, typename FT, int G> __device__ __forceinline__ int compact(Tile
         for (int k = 0; k < G / 64; k++) n += (int)L.gcnt[k];
         return n;
     } else if constexpr (K % 8 == 0) {
-        // flags are 0/1 bytes: a 64-bit word holds 8 of them
-        unsigned long long *w = (unsigned long long *)&L.cf[lane * K];
+        // flags are 0/1 bytes: a lane's 64-bit word holds the 8 of its row
+        static_assert(E == 8, "a row per lane");
+        unsigned long long *w = (unsigned long long *)&L.cf[Geo<E>::cfi(lane * K)];
         unsigned long long x[K / 8];
 #pragma unroll
         for (int j = 0; j < K / 8; j++) {
@@ -330,11 +347,10 @@ template <int E, typename FT, int G> __device__ __forceinline__ int compact(Tile
             cnt += (uint32_t)__popcll(x[j]);
         }
         uint32_t pre = 0, total = 0;
-        const unsigned long long lt = (1ull << lane) - 1ull;
 #pragma unroll
         for (int b = 0; (1 << b) <= K; b++) {
             const unsigned long long m = __ballot((cnt >> b) & 1u);
-            pre += (uint32_t)__popcll(m & lt) << b;
+            pre += lanes_below(m) << b;
             total += (uint32_t)__popcll(m) << b;
         }
 #pragma unroll
@@ -349,14 +365,14 @@ template <int E, typename FT, int G> __device__ __forceinline__ int compact(Tile
                 out[pre++] = (uint16_t)(lane * K + j * 8 + bit);
                 y &= y - 1u;
             }
-            if (x[j]) w[j] = 0ull;
+            w[j] = 0ull;
         }
         wave_sync();
         return (int)total;
     } else {
         if (lane * K < Geo<E>::V) {
 #pragma unroll
-            for (int j = 0; j < K; j++) cnt += L.cf[lane * K + j] != 0;
+            for (int j = 0; j < K; j++) cnt += L.cf[Geo<E>::cfi(lane * K + j)] != 0;
         }
         uint32_t pre = 0, total = 0;
         const unsigned long long lt = (1ull << lane) - 1ull;
@@ -370,9 +386,9 @@ template <int E, typename FT, int G> __device__ __forceinline__ int compact(Tile
 #pragma unroll
             for (int j = 0; j < K; j++) {
                 const int p = lane * K + j;
-                if (L.cf[p]) {
+                if (L.cf[Geo<E>::cfi(p)]) {
                     out[pre++] = (uint16_t)p;
-                    L.cf[p] = 0;
+                    L.cf[Geo<E>::cfi(p)] = 0;
                 }
             }
         }
@@ -410,6 +426,7 @@ __device__ __forceinline__ void mark_nbrs(TileLds<E, FT, G> &L, int p, int d, do
     // carries FL_UPD, so its out-of-interior index is never marked
     const int od[6] = {-Gm::OX, Gm::OX, -Gm::OY, Gm::OY, -Gm::OZ, Gm::OZ};
     const int op[6] = {-E * E, E * E, -E, E, -1, 1};
+    const int oc[6] = {-Gm::CX, Gm::CX, -Gm::CY, Gm::CY, -1, 1};
     uint8_t f[6];
     double v[6];
 #pragma unroll
@@ -418,7 +435,13 @@ __device__ __forceinline__ void mark_nbrs(TileLds<E, FT, G> &L, int p, int d, do
         v[k] = L.T[d + od[k]];
     }
 #pragma unroll
-    for (int k = 0; k < 6; k++) mark_cand(L, (f[k] & FL_UPD) && fabs(v[k]) > a, p + op[k]);
+    for (int k = 0; k < 6; k++) {
+        const bool on = (f[k] & FL_UPD) && fabs(v[k]) > a;
+        if constexpr (TileLds<E, FT, G>::BITS)
+            mark_cand(L, on, p + op[k]);
+        else
+            L.cf[(on ? Gm::cfi(p) : Gm::spare((int)__lane_id())) + oc[k]] = 1;
+    }
 }
 
 // A domain cell is a source of the relaxation when it is a seed, or when its
@@ -556,6 +579,11 @@ __device__ __forceinline__ int relax(KParams P, TileLds<E, FT, G> &L, double h, 
         sp.s[2] = P->sp.s[2];
     }
     const int r = Grp<G>::rank_here();
+    // the lane's spare candidate byte, formed once (opaque, so that the choice
+    // between it and the cell's byte stays a select)
+    lds_byte *cf = (lds_byte *)&L.cf[0];
+    lds_byte *sp0 = cf + Gm::spare(r & 63);
+    asm volatile("" : "+v"(sp0));
     int n = compact(L);
     int rounds = 0;
     while (n > 0) {
@@ -576,27 +604,47 @@ __device__ __forceinline__ int relax(KParams P, TileLds<E, FT, G> &L, double h, 
             if constexpr (G == 64) wave_sync();
             if (ch) {
                 const int d = Gm::domp(p);
-                const uint8_t fo = L.fl[d];
-                // reopened: the old value was already a source.  The level
-                // never drops below the bound of the tile's previous march, so
-                // this covers every value that march released.
-                ws.n_reopen += (fo >> 3) & 1u;  // FL_SRC
                 L.T[d] = nv;
-                // one-sided tiles: nv is positive and finite (it beat vp)
-                const bool src = TWO ? is_source(nv, 0, th) : nv <= th[1];
-                L.fl[d] = fo | (src ? (uint8_t)(FL_CHG | FL_SRC) : (uint8_t)FL_CHG);
+                bool src;
+                if constexpr (TWO) {
+                    // reopened: the old value was already a source.  The level
+                    // never drops below the bound of the tile's previous march,
+                    // so this covers every value that march released.
+                    const uint8_t fo = L.fl[d];
+                    ws.n_reopen += (fo >> 3) & 1u;  // FL_SRC
+                    src = is_source(nv, 0, th);
+                    L.fl[d] = fo | (src ? (uint8_t)(FL_CHG | FL_SRC) : (uint8_t)FL_CHG);
+                } else {
+                    // one-sided tiles: nv is positive and finite (it beat vp),
+                    // and only updatable cells change.  Such a cell is a source
+                    // exactly when its value is within the level, so its flags
+                    // are known without reading them.
+                    ws.n_reopen += vp <= th[1] ? 1u : 0u;
+                    src = nv <= th[1];
+                    L.fl[d] = src ? (uint8_t)(FL_UPD | FL_CHG | FL_SRC) : (uint8_t)(FL_UPD | FL_CHG);
+                }
                 const double a = TWO ? fabs(nv) : nv;
                 if (src) {
                     // mark the downwind interior neighbours.  Seeds and
                     // impassable cells may be marked too: their LDS speed is
                     // 0, so their solve gives +inf and changes nothing.
                     const int i0 = p >> (2 * Gm::LOG), i1 = (p >> Gm::LOG) & (E - 1), i2 = p & (E - 1);
-                    mark_cand(L, i0 > 0 && na[0] > a, p - E * E);
-                    mark_cand(L, i0 < E - 1 && na[1] > a, p + E * E);
-                    mark_cand(L, i1 > 0 && na[2] > a, p - E);
-                    mark_cand(L, i1 < E - 1 && na[3] > a, p + E);
-                    mark_cand(L, i2 > 0 && na[4] > a, p - 1);
-                    mark_cand(L, i2 < E - 1 && na[5] > a, p + 1);
+                    if constexpr (TileLds<E, FT, G>::BITS) {
+                        mark_cand(L, i0 > 0 && na[0] > a, p - E * E);
+                        mark_cand(L, i0 < E - 1 && na[1] > a, p + E * E);
+                        mark_cand(L, i1 > 0 && na[2] > a, p - E);
+                        mark_cand(L, i1 < E - 1 && na[3] > a, p + E);
+                        mark_cand(L, i2 > 0 && na[4] > a, p - 1);
+                        mark_cand(L, i2 < E - 1 && na[5] > a, p + 1);
+                    } else {
+                        lds_byte *c = cf + Gm::cfi(p);
+                        (na[0] > a ? c : sp0)[-Gm::CX] = 1;
+                        (na[1] > a ? c : sp0)[Gm::CX] = 1;
+                        (na[2] > a ? c : sp0)[-Gm::CY] = 1;
+                        (na[3] > a ? c : sp0)[Gm::CY] = 1;
+                        (i2 > 0 && na[4] > a ? c : sp0)[-1] = 1;
+                        (i2 < E - 1 && na[5] > a ? c : sp0)[1] = 1;
+                    }
                 }
             }
             if constexpr (G == 64) wave_sync();
@@ -847,7 +895,7 @@ __device__ __forceinline__ void tile_march(KParams P0, TileLds<E, FT, G> &L, con
                 else
                     L.F[p] = fixed ? (FT)0 : fminf(fi[j], 3.402823466e38f);
                 L.fl[d] = f8;
-                if constexpr (!TileLds<E, FT, G>::BITS) L.cf[p] = 0;
+                if constexpr (!TileLds<E, FT, G>::BITS) L.cf[Gm::cfi(p)] = 0;
             }
         }
     };

@@ -21,11 +21,24 @@ template <int E> struct Geo {
     static constexpr int LOG = (E == 4) ? 2 : (E == 8) ? 3 : 4;
     __host__ __device__ static constexpr int dom(int i0, int i1, int i2) { return ((i0 + 1) * D + (i1 + 1)) * D + (i2 + 1); }
     __host__ __device__ static constexpr int domp(int p) { return dom(p >> (2 * LOG), (p >> LOG) & (E - 1), p & (E - 1)); }
-    // candidate bytes of a one-wavefront group: one per interior cell, then
-    // one spare dword per lane, which a lane that does not mark writes
-    // instead (so a mark is a store under no lane mask, in distinct banks)
-    static constexpr int CFB = V + 4 * 64;
-    __host__ __device__ static constexpr int spare(int lane) { return V + 4 * lane; }
+    // Candidate bytes of a one-wavefront group.  Rows of E cells along axis 2
+    // with a halo row on either side along axes 0 and 1, so that a mark for a
+    // neighbour across those faces lands in a row nobody reads and needs no
+    // test; cfi() is the byte of interior index p.  Behind them one spare dword
+    // per lane, which a lane that does not mark writes instead, at the same
+    // offset from it as the mark from its cell (a mark is then a store under no
+    // lane mask, its offset an immediate): the stores below the spares reach
+    // the last halo rows, those above them the bytes that end the array.
+    // (With one byte per interior cell a mark tested its cell's coordinates and
+    // formed two addresses: 36 vector instructions for six marks, now 18.)
+    static constexpr int CX = D * E, CY = E;  // byte offsets of a neighbour along axes 0 and 1 (axis 2: 1)
+    static constexpr int CFP = D * D * E;
+    static constexpr int CFB = CFP + 4 * 64 + CX;
+    __host__ __device__ static constexpr int cfi(int p)
+    {
+        return (((p >> (2 * LOG)) + 1) * D + ((p >> LOG) & (E - 1)) + 1) * E + (p & (E - 1));
+    }
+    __host__ __device__ static constexpr int spare(int lane) { return CFP + 4 * lane; }
 };
 
 
