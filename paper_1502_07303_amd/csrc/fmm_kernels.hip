@@ -1077,80 +1077,103 @@ __device__ __forceinline__ void tile_march(KParams P0, TileLds<E, FT, G> &L, con
     }
     PROF_ADD(10 + mode, 1);
 
-    // ---- write back (every cell on the first write of the tile, else the
-    // changed ones) and classify the changed boundary cells per face: a new
-    // source value is sent at once (the neighbour re-marches, KNOWN_OLD of Alg.
-    // 15), a band value only joins the neighbour's pending minimum (BAND_OLD).
-    uint32_t fsrc = 0, fany = 0;
+    // ---- write back every cell on the tile's first write, else the changed
+    // ones.  The flags and values of a thread's cells are read together (one
+    // LDS round trip).
 #ifdef FMM_PROFILE
     bool any_chg = false;
 #endif
-    // the flags and values of a thread's cells are read together (one LDS
-    // round trip); the changed-cell flags are kept as a bit mask
     constexpr int NW = V / G;
-    static_assert(NW <= 32, "cells per thread");
-    double vw[NW];
-    uint32_t chgm = 0;
+    {
+        double vw[NW];
+        uint8_t fw[NW];
 #pragma unroll
-    for (int j = 0; j < NW; j++) {
-        const int d = Gm::domp(rk + G * j);
-        const uint8_t fj = L.fl[d];
-        vw[j] = L.T[d];
-        chgm |= (uint32_t)((fj >> 2) & 1u) << j;  // FL_CHG
-    }
+        for (int j = 0; j < NW; j++) {
+            const int d = Gm::domp(rk + G * j);
+            fw[j] = L.fl[d];
+            vw[j] = L.T[d];
+        }
 #pragma unroll
-    for (int j = 0; j < NW; j++) {
-        const int p = rk + G * j;
-        const int d = Gm::domp(p);
-        const bool chg = (chgm >> j) & 1u;
+        for (int j = 0; j < NW; j++) {
+            if ((fw[j] & FL_CHG) || fresh) Tt[tbase + rk + G * j] = vw[j];
 #ifdef FMM_PROFILE
-        any_chg |= chg;
+            any_chg |= (fw[j] & FL_CHG) != 0;
 #endif
-        if (!(chg || fresh)) continue;
-        const int i0 = p >> (2 * Gm::LOG), i1 = (p >> Gm::LOG) & (E - 1), i2 = p & (E - 1);
-        const double v = vw[j];
-        Tt[tbase + p] = v;
-        if (i2 == 0) P->Zf[((size_t)t * 2 + 0) * FACE + i0 * E + i1] = v;
-        if (i2 == E - 1) P->Zf[((size_t)t * 2 + 1) * FACE + i0 * E + i1] = v;
-        if (!chg) continue;
-        // faces this boundary cell lies on whose neighbouring cell it can
-        // improve: the halo holds that cell's value as loaded, an upper bound
-        // of its current value (values only decrease), and a root from v
-        // exceeds |v|; so |v| >= the halo magnitude means nothing to send
-        const double av = fabs(v);
-        const uint32_t fm = (i0 == 0 && av < fabs(L.T[d - Gm::OX]) ? 1u : 0u) |
-                            (i0 == E - 1 && av < fabs(L.T[d + Gm::OX]) ? 2u : 0u) |
-                            (i1 == 0 && av < fabs(L.T[d - Gm::OY]) ? 4u : 0u) |
-                            (i1 == E - 1 && av < fabs(L.T[d + Gm::OY]) ? 8u : 0u) |
-                            (i2 == 0 && av < fabs(L.T[d - Gm::OZ]) ? 16u : 0u) |
-                            (i2 == E - 1 && av < fabs(L.T[d + Gm::OZ]) ? 32u : 0u);
-        if (!fm) continue;
-        fany |= fm;
-        if (is_source(v, 0, bnd)) {
-            fsrc |= fm;
-        } else {
-            const int sd = v < 0.0 ? 0 : 1;
-            const unsigned long long b = bits_of(fabs(v));
-            for (int f = 0; f < 6; f++)
-                if ((fm >> f) & 1u) atomicMin(&L.bm[f * 2 + sd], b);
         }
     }
 #ifdef FMM_PROFILE
     PROF_ADD(15, (__ballot(any_chg) == 0ull && mode == MODE_M2) ? 1 : 0);
 #endif
+    // Classify the changed boundary cells face by face (a pass takes a whole
+    // face of an 8^3 tile, so its number and its cells' offsets are constants):
+    // a new source value is sent at once (the neighbour re-marches, KNOWN_OLD
+    // of Alg. 15), a band value only joins the neighbour's pending minimum
+    // (BAND_OLD).  A value is passed on only if it can improve the cell across
+    // the face: the halo holds that cell's value as loaded, an upper bound of
+    // its current value (values only decrease), and a root from v exceeds |v|;
+    // so |v| >= the halo magnitude means nothing to send.  The axis-2 faces
+    // also go to the tile's face buffer here.
+    // (Testing each changed cell against its up to three faces took twice the
+    // instructions: 1024^3 at 3.5h 204.0 and 197.4 ms, 64^3 shells 7.34 and 6.87.)
     uint32_t srcFaces = 0, anyFaces = 0;
-    if constexpr (G == 64) {
+    {
+        constexpr int NQ = (6 * FACE + G - 1) / G;
+        uint32_t fsrc = 0, fany = 0;
+        double v[NQ], vh[NQ];
+        uint8_t fi[NQ];
 #pragma unroll
-        for (int f = 0; f < 6; f++) {
-            if (__ballot((fsrc >> f) & 1u)) srcFaces |= 1u << f;
-            if (__ballot((fany >> f) & 1u)) anyFaces |= 1u << f;
+        for (int j = 0; j < NQ; j++) {
+            const int q = rk + G * j;
+            v[j] = vh[j] = FMM_INF;  // a thread past the last face cell sends nothing
+            fi[j] = 0;
+            if (FACE * 6 % G != 0 && q >= 6 * FACE) continue;
+            const int f = FACE == G ? j : q / FACE, uv = q - f * FACE, u = uv / E, w = uv - u * E;
+            int c0, c1, c2;
+            face_cell<E>(f, u, w, c0, c1, c2);
+            vh[j] = L.T[Gm::dom(c0, c1, c2)];
+            face_inner<E>(f, c0, c1, c2);
+            const int di = Gm::dom(c0, c1, c2);
+            v[j] = L.T[di];
+            fi[j] = L.fl[di];
         }
-        wave_sync();
-    } else {
-        // also orders every write of the band minima bm before they are read
-        const uint32_t m = grp_or(L, fsrc | (fany << 8));
-        srcFaces = m & 0x3Fu;
-        anyFaces = (m >> 8) & 0x3Fu;
+#pragma unroll
+        for (int j = 0; j < NQ; j++) {
+            const int q = rk + G * j;
+            const int f = FACE == G ? j : q / FACE;
+            const bool chg = fi[j] & FL_CHG;
+            if (f >= 4 && f < 6 && (chg || fresh)) P->Zf[(size_t)t * 2 * FACE + q - 4 * FACE] = v[j];
+            const double av = fabs(v[j]);
+            const bool pass = chg && av < fabs(vh[j]);
+            const int sd = v[j] < 0.0 ? 0 : 1;
+            const bool src = pass && av <= bnd[sd];
+            const unsigned long long b = bits_of(av);
+            if constexpr (FACE == G && G == 64) {
+                const bool anyf = __ballot(pass) != 0ull, srcf = __ballot(src) != 0ull;
+                if (anyf) anyFaces |= 1u << f;
+                if (srcf) srcFaces |= 1u << f;
+                // only a face without new sources uses its band minimum
+                if (anyf && !srcf && pass) atomicMin(&L.bm[f * 2 + sd], b);
+            } else {
+                if (pass) fany |= 1u << f;
+                if (src) fsrc |= 1u << f;
+                if (pass && !src) atomicMin(&L.bm[f * 2 + sd], b);
+            }
+        }
+        if constexpr (FACE == G && G == 64) {
+            wave_sync();
+        } else if constexpr (G == 64) {
+#pragma unroll
+            for (int f = 0; f < 6; f++) {
+                if (__ballot((fsrc >> f) & 1u)) srcFaces |= 1u << f;
+                if (__ballot((fany >> f) & 1u)) anyFaces |= 1u << f;
+            }
+            wave_sync();
+        } else {
+            // also orders every write of the band minima bm before they are read
+            const uint32_t m = grp_or(L, fsrc | (fany << 8));
+            srcFaces = m & 0x3Fu;
+            anyFaces = (m >> 8) & 0x3Fu;
+        }
     }
     if (fresh && rk == 0) __hip_atomic_store(&P->visit[t], phase + 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 
@@ -1456,15 +1479,19 @@ __device__ __forceinline__ void run_phase(KParams P, TileLds<E, FT, G> &L, WgSha
         S.gmin1[wid] = ws.gmin1;
     }
     __syncthreads();
-    if (threadIdx.x == 0) {
-        uint32_t tl = 0, td = 0;
+    // thread 0 appends to the live list and thread 1 to the dirty list (both
+    // replies are under way together), thread 2 reduces
+    if (threadIdx.x < 2) {
+        uint32_t tot = 0;
+        for (int w = 0; w < NW; w++) tot += threadIdx.x ? S.cntD[w] : S.cntL[w];
+        const uint32_t base = tot ? atomicAdd(threadIdx.x ? &cur.d_len : &nxt.live_len, tot) : 0u;
+        if (threadIdx.x)
+            S.baseD = base;
+        else
+            S.baseL = base;
+    }
+    if (threadIdx.x == 2) {
         S.drained = 0;
-        for (int w = 0; w < NW; w++) {
-            tl += S.cntL[w];
-            td += S.cntD[w];
-        }
-        S.baseL = tl ? atomicAdd(&nxt.live_len, tl) : 0u;
-        S.baseD = td ? atomicAdd(&cur.d_len, td) : 0u;
         // wavefronts holding the same problem are combined
         for (int w = 0; w < NW; w++) {
             const uint32_t j = S.inst[w];
