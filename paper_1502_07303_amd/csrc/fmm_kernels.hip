@@ -998,9 +998,9 @@ __device__ __forceinline__ void tile_march(KParams P0, TileLds<E, FT, G> &L, con
     // ---- ordered relaxation.  Sources at level th are the seeds and the
     // cells with |T| <= th of their side (the KNOWN-class points of Alg. 11).
     // The level starts at the bound of the tile's previous march and climbs to
-    // this restart's bound in steps th = (smallest pending band value) + inner,
-    // so values become sources in increasing order, as the heap of Alg. 12
-    // would release them, up to the step width.
+    // this restart's bound, at once or in steps th = (smallest pending band
+    // value) + inner, so that values become sources in increasing order, as the
+    // heap of Alg. 12 would release them, up to the step width.
     PROF_CLOCK(t_loaded);
     PROF_ADD(2, t_loaded - t_begin);
     const bool init = mode == MODE_INIT;
@@ -1064,22 +1064,35 @@ __device__ __forceinline__ void tile_march(KParams P0, TileLds<E, FT, G> &L, con
         }
     }
     Grp<G>::sync();
+    // Without inner steps (P->inner = +inf) there are at most two levels: the
+    // one the march starts at and the restart's bound, to which every value
+    // within it is released at once.  The pending minimum is not needed on the
+    // way then; it is gathered by the passes that write the tile back (1024^3
+    // at 3.5h 197.0 ms with the scans, 190.6 without, 64^3 shells 6.70 and 6.41).
+    // With inner steps every level starts from a scan for it.
     int rounds = 0;
-    double tm0, tm1;
     PROF_CLOCK(t_marked);
     PROF_ADD(3, t_marked - t_loaded);
-    for (;;) {
+    for (bool first = true;; first = false) {
         PROF_CLOCK(t_r0);
         rounds += two ? relax<E, FT, G, AN, true>(P, L, G0.h, th, ws) : relax<E, FT, G, AN, false>(P, L, G0.h, th, ws);
         PROF_CLOCK(t_r1);
         PROF_ADD(4, t_r1 - t_r0);
         PROF_ADD(8, 1);
-        band_min(L, th, tm0, tm1);
-        const bool more0 = tm0 < FMM_INF && tm0 <= bnd[0];
-        const bool more1 = tm1 < FMM_INF && tm1 <= bnd[1];
-        if (!(more0 || more1)) break;
-        const double nt[2] = {more0 ? fmin(tm0 + P->inner, bnd[0]) : th[0],
-                              more1 ? fmin(tm1 + P->inner, bnd[1]) : th[1]};
+        double nt[2];
+        if (P->inner == FMM_INF) {
+            if (!first || (th[0] >= bnd[0] && th[1] >= bnd[1])) break;
+            nt[0] = fmax(th[0], bnd[0]);
+            nt[1] = fmax(th[1], bnd[1]);
+        } else {
+            double tm0, tm1;
+            band_min(L, th, tm0, tm1);
+            const bool more0 = tm0 < FMM_INF && tm0 <= bnd[0];
+            const bool more1 = tm1 < FMM_INF && tm1 <= bnd[1];
+            if (!(more0 || more1)) break;
+            nt[0] = more0 ? fmin(tm0 + P->inner, bnd[0]) : th[0];
+            nt[1] = more1 ? fmin(tm1 + P->inner, bnd[1]) : th[1];
+        }
         mark_new_sources(L, th, nt);
         th[0] = nt[0];
         th[1] = nt[1];
@@ -1100,6 +1113,18 @@ __device__ __forceinline__ void tile_march(KParams P0, TileLds<E, FT, G> &L, con
     bool any_chg = false;
 #endif
     constexpr int NW = V / G;
+    // the pending minimum per side: band values above the level in the tile,
+    // and halo values above it next to a cell that is not yet a source (they
+    // become sources of this tile later)
+    double tm0 = FMM_INF, tm1 = FMM_INF;
+    auto pending = [&](bool on, double v) {
+        const double a = on ? fabs(v) : FMM_INF;
+        const bool neg = v < 0.0;
+        if (neg)
+            tm0 = fmin(tm0, a > th[0] ? a : FMM_INF);
+        else
+            tm1 = fmin(tm1, a > th[1] ? a : FMM_INF);
+    };
     {
         double vw[NW];
         uint8_t fw[NW];
@@ -1112,6 +1137,7 @@ __device__ __forceinline__ void tile_march(KParams P0, TileLds<E, FT, G> &L, con
 #pragma unroll
         for (int j = 0; j < NW; j++) {
             if ((fw[j] & FL_CHG) || fresh) Tt[tbase + rk + G * j] = vw[j];
+            pending((fw[j] & FL_UPD) != 0, vw[j]);
 #ifdef FMM_PROFILE
             any_chg |= (fw[j] & FL_CHG) != 0;
 #endif
@@ -1136,17 +1162,19 @@ __device__ __forceinline__ void tile_march(KParams P0, TileLds<E, FT, G> &L, con
         constexpr int NQ = (6 * FACE + G - 1) / G;
         uint32_t fsrc = 0, fany = 0;
         double v[NQ], vh[NQ];
-        uint8_t fi[NQ];
+        uint8_t fi[NQ], fh[NQ];
 #pragma unroll
         for (int j = 0; j < NQ; j++) {
             const int q = rk + G * j;
             v[j] = vh[j] = FMM_INF;  // a thread past the last face cell sends nothing
-            fi[j] = 0;
+            fi[j] = fh[j] = 0;
             if (FACE * 6 % G != 0 && q >= 6 * FACE) continue;
             const int f = FACE == G ? j : q / FACE, uv = q - f * FACE, u = uv / E, w = uv - u * E;
             int c0, c1, c2;
             face_cell<E>(f, u, w, c0, c1, c2);
-            vh[j] = L.T[Gm::dom(c0, c1, c2)];
+            const int dh = Gm::dom(c0, c1, c2);
+            vh[j] = L.T[dh];
+            fh[j] = L.fl[dh];
             face_inner<E>(f, c0, c1, c2);
             const int di = Gm::dom(c0, c1, c2);
             v[j] = L.T[di];
@@ -1157,6 +1185,7 @@ __device__ __forceinline__ void tile_march(KParams P0, TileLds<E, FT, G> &L, con
             const int q = rk + G * j;
             const int f = FACE == G ? j : q / FACE;
             const bool chg = fi[j] & FL_CHG;
+            pending(!(fh[j] & FL_SEED) && (fi[j] & (FL_UPD | FL_SRC)) == FL_UPD, vh[j]);
             if (f >= 4 && f < 6 && (chg || fresh)) P->Zf[(size_t)t * 2 * FACE + q - 4 * FACE] = v[j];
             const double av = fabs(v[j]);
             const bool pass = chg && av < fabs(vh[j]);
@@ -1191,6 +1220,7 @@ __device__ __forceinline__ void tile_march(KParams P0, TileLds<E, FT, G> &L, con
             anyFaces = (m >> 8) & 0x3Fu;
         }
     }
+    grp_min2(L, tm0, tm1);
     if (fresh && rk == 0) __hip_atomic_store(&P->visit[t], phase + 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 
     if (rk == 0) {
