@@ -456,8 +456,8 @@ __device__ __forceinline__ bool is_source(double v, uint8_t fl, const double bnd
 }
 
 // r = h / F of interior point p.  Fixed cells (seeds, impassable cells) hold
-// speed 0, whose r is NaN, or the r = +inf of an FP64 slot: no root from either
-// beats a value.
+// speed 0, whose r is NaN, or r = +inf or NaN in an FP64 slot: no root from
+// either beats a value.
 template <int E, typename FT, int G>
 __device__ __forceinline__ double cell_r(const TileLds<E, FT, G> &L, int p, double h)
 {
@@ -885,36 +885,74 @@ __device__ __forceinline__ void tile_march(KParams P0, TileLds<E, FT, G> &L, con
             }
         }
     };
+    // A value is a source at the starting level when it lies within [src_lo,
+    // src_hi] (is_source() for a cell that is no seed: both levels are negative,
+    // and then nothing lies within, or neither is).  Two compares per cell, with
+    // seeds put right afterwards in the tiles that hold any: 1024^3 at 3.5h
+    // 190.4 and 185.8 ms, 64^3 shells 6.40 and 6.27.
+    const bool wide_h = !(G0.h > 0x1p-300 && G0.h < 0x1p300);
+    const double src_hi = fmin(th0[1], 0x1.fffffffffffffp+1023);
+    const double src_lo = th0[0] >= 0.0 ? -fmin(th0[0], 0x1.fffffffffffffp+1023) : 0.0;
     auto store_interior = [&](int j0, bool hasSeed, bool fresh) {
+        if (fresh) {
+#pragma unroll
+            for (int j = 0; j < CI; j++) vi[j] = FMM_INF;
+        }
+        if constexpr (sizeof(FT) == 8) {
+#pragma unroll
+            for (int j = 0; j < CI; j++) {
+                const double f = (double)fi[j];
+                fi[j] = (FT)(f > 0.0 ? G0.h / f : __builtin_nan(""));
+            }
+        }
 #pragma unroll
         for (int j = 0; j < CI; j++) {
             const int p = rk + G * (j0 + j);
             if (p < V) {
                 const int d = Gm::domp(p);
-                const bool seed = hasSeed && ((mask[p >> 6] >> (p & 63)) & 1ull);
-                const double tv = fresh ? FMM_INF : vi[j];
-                uint8_t f8 = seed ? FL_SEED : ((double)fi[j] > 0.0 ? FL_UPD : 0);
-                if (is_source(tv, f8, th0)) f8 |= FL_SRC;
+                const double tv = vi[j];
+                // impassable cells (F <= 0 or NaN) keep speed 0 or r = NaN in
+                // LDS, so the relaxation never changes them.  An infinite FP32
+                // speed (r = 0) is kept as the largest finite one: the march's
+                // division wants a finite divisor, and h / FLT_MAX is below the
+                // rounding of any value it is added to unless that value is
+                // itself below about 1e-26.
+                bool free;
+                if constexpr (sizeof(FT) == 8) {
+                    free = fi[j] == fi[j];
+                    L.F[p] = fi[j];
+                } else {
+                    free = fi[j] > 0.0f;
+                    L.F[p] = __builtin_amdgcn_fmed3f(fi[j], 0.0f, 3.402823466e38f);
+                }
+                const uint8_t f8 = free ? FL_UPD : 0;
+                const bool src = (int)(tv >= src_lo) & (int)(tv <= src_hi);
+                L.fl[d] = src ? (uint8_t)(f8 | FL_SRC) : f8;
                 anyneg |= tv < 0.0;
                 L.T[d] = tv;
-                // seeds and impassable cells (F <= 0 or NaN) keep speed 0 in
-                // LDS (r = h/0 = +inf), so the relaxation never changes them.
-                // An FP64 slot holds r = h / F itself, computed once per cell
-                // with the same expression as for FP32 speeds.
-                const bool fixed = seed || !((double)fi[j] > 0.0);
-                // An infinite FP32 speed (r = 0) is kept as the largest finite
-                // one: the march's division wants a finite divisor, and
-                // h / FLT_MAX is below the rounding of any value it is added to
-                // unless that value is itself below about 1e-26.
-                if constexpr (sizeof(FT) == 8)
-                    L.F[p] = fixed ? FMM_INF : G0.h / (double)fi[j];
-                else
-                    L.F[p] = fixed ? (FT)0 : fminf(fi[j], 3.402823466e38f);
-                L.fl[d] = f8;
-                if constexpr (!TileLds<E, FT, G>::BITS) L.cf[Gm::cfi(p)] = 0;
+            }
+        }
+        if (hasSeed) {
+            // rare: seeds are fixed, and sources
+#pragma unroll 1
+            for (int j = 0; j < CI; j++) {
+                const int p = rk + G * (j0 + j);
+                if (p < V && ((mask[p >> 6] >> (p & 63)) & 1ull)) {
+                    const int d = Gm::domp(p);
+                    L.fl[d] = fabs(L.T[d]) < FMM_INF ? (uint8_t)(FL_SEED | FL_SRC) : (uint8_t)FL_SEED;
+                    L.F[p] = sizeof(FT) == 8 ? (FT)FMM_INF : (FT)0;
+                }
             }
         }
     };
+    // candidate flags start clear (a lane's row at once in an 8^3 tile)
+    if constexpr (!TileLds<E, FT, G>::BITS) {
+        if constexpr (E == 8) {
+            *(unsigned long long *)&L.cf[Gm::cfi(rk * 8)] = 0ull;
+        } else {
+            for (int p = rk; p < V; p += G) L.cf[Gm::cfi(p)] = 0;
+        }
+    }
     // the first interior chunk and every face-halo read are issued before
     // any of them is used.  The halo reads take no branch: a face on the
     // grid boundary reads the tile's own cells (a valid address) and its
@@ -969,9 +1007,9 @@ __device__ __forceinline__ void tile_march(KParams P0, TileLds<E, FT, G> &L, con
             const bool plus = f & 1;
             int c0, c1, c2;
             face_cell<E>(f, u, w, c0, c1, c2);
-            double v = FMM_INF;
-            uint8_t fl = 0;
-            if (vis_h[j] != 0 && vis_h[j] <= phase) v = vh[j];
+            const double v = vis_h[j] - 1u < phase ? vh[j] : FMM_INF;  // written in phases 1 to phase - 1
+            const bool src = (int)(v >= src_lo) & (int)(v <= src_hi);
+            uint8_t fl = src ? FL_SRC : 0;
             if (tf_h[j] & TF_SEED) {
                 // rare: the neighbour holds seeds; fetch its seed bit
                 const uint32_t ts = ax == 0 ? tsx : ax == 1 ? tsy : 1u;
@@ -980,10 +1018,10 @@ __device__ __forceinline__ void tile_march(KParams P0, TileLds<E, FT, G> &L, con
                 const int n1c = ax == 1 ? (plus ? 0 : E - 1) : c1;
                 const int n2c = ax == 2 ? (plus ? 0 : E - 1) : c2;
                 const int pn = (n0c * E + n1c) * E + n2c;
-                if ((P->mask[(size_t)tnb * P->mask_words + (pn >> 6)] >> (pn & 63)) & 1ull) fl = FL_SEED;
+                if ((P->mask[(size_t)tnb * P->mask_words + (pn >> 6)] >> (pn & 63)) & 1ull)
+                    fl = fabs(v) < FMM_INF ? (uint8_t)(FL_SEED | FL_SRC) : (uint8_t)FL_SEED;
             }
             const int d = Gm::dom(c0, c1, c2);
-            if (is_source(v, fl, th0)) fl |= FL_SRC;
             anyneg |= v < 0.0;
             L.T[d] = v;
             L.fl[d] = fl;
