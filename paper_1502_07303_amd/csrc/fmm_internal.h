@@ -204,7 +204,7 @@ struct Params {
     InstCtl *ictl;        // per-problem restart state and statistics
     uint32_t *tinst;      // problem of each tile
     double *Tt;       // tiled working T
-    void *Ft;         // tiled speeds (type of F)
+    void *Ft;         // tiled speeds (type of F; FP64: h / F)
     double *Zf;       // per tile: its i2 = 0 and i2 = E-1 faces
     Ctrl *ctrl;
     TileMeta *meta;

@@ -890,7 +890,6 @@ __device__ __forceinline__ void tile_march(KParams P0, TileLds<E, FT, G> &L, con
     // and then nothing lies within, or neither is).  Two compares per cell, with
     // seeds put right afterwards in the tiles that hold any: 1024^3 at 3.5h
     // 190.4 and 185.8 ms, 64^3 shells 6.40 and 6.27.
-    const bool wide_h = !(G0.h > 0x1p-300 && G0.h < 0x1p300);
     const double src_hi = fmin(th0[1], 0x1.fffffffffffffp+1023);
     const double src_lo = th0[0] >= 0.0 ? -fmin(th0[0], 0x1.fffffffffffffp+1023) : 0.0;
     auto store_interior = [&](int j0, bool hasSeed, bool fresh) {
@@ -898,33 +897,16 @@ __device__ __forceinline__ void tile_march(KParams P0, TileLds<E, FT, G> &L, con
 #pragma unroll
             for (int j = 0; j < CI; j++) vi[j] = FMM_INF;
         }
-        if constexpr (sizeof(FT) == 8) {
-#pragma unroll
-            for (int j = 0; j < CI; j++) {
-                const double f = (double)fi[j];
-                fi[j] = (FT)(f > 0.0 ? G0.h / f : __builtin_nan(""));
-            }
-        }
 #pragma unroll
         for (int j = 0; j < CI; j++) {
             const int p = rk + G * (j0 + j);
             if (p < V) {
                 const int d = Gm::domp(p);
                 const double tv = vi[j];
-                // impassable cells (F <= 0 or NaN) keep speed 0 or r = NaN in
-                // LDS, so the relaxation never changes them.  An infinite FP32
-                // speed (r = 0) is kept as the largest finite one: the march's
-                // division wants a finite divisor, and h / FLT_MAX is below the
-                // rounding of any value it is added to unless that value is
-                // itself below about 1e-26.
-                bool free;
-                if constexpr (sizeof(FT) == 8) {
-                    free = fi[j] == fi[j];
-                    L.F[p] = fi[j];
-                } else {
-                    free = fi[j] > 0.0f;
-                    L.F[p] = __builtin_amdgcn_fmed3f(fi[j], 0.0f, 3.402823466e38f);
-                }
+                // impassable cells hold speed 0 or r = NaN (tiled_speed()), so
+                // the relaxation never changes them
+                const bool free = sizeof(FT) == 8 ? fi[j] == fi[j] : fi[j] > (FT)0;
+                L.F[p] = fi[j];
                 const uint8_t f8 = free ? FL_UPD : 0;
                 const bool src = (int)(tv >= src_lo) & (int)(tv <= src_hi);
                 L.fl[d] = src ? (uint8_t)(f8 | FL_SRC) : f8;
@@ -1810,8 +1792,23 @@ __global__ void k_init_ws(Params P, int E)
     for (int64_t i = i0; i < nm; i += stride) P.mask[i] = 0ull;
 }
 
-// Tiled copy of one problem's speeds (0 outside its grid) and the problem
-// index of each of its tiles.
+// What the tiled copy of the speeds holds for a speed f: the march's form of
+// it, computed once per solve.
+// FP64: r = h / f, NaN for an impassable point (f <= 0 or NaN).  (Dividing in
+// every tile load instead: 64-problem batch 33.5 ms, now 32.9, 64^3 shells
+// 6.27 and 6.15.)
+__device__ __forceinline__ double tiled_speed(double f, double h) { return f > 0.0 ? h / f : __builtin_nan(""); }
+// FP32: the speed, 0 for an impassable point, an infinite one (r = 0) as the
+// largest finite one: the march's division wants a finite divisor, and h /
+// FLT_MAX is below the rounding of any value it is added to unless that value
+// is itself below about 1e-26.
+__device__ __forceinline__ float tiled_speed(float f, double)
+{
+    return __builtin_amdgcn_fmed3f(f, 0.0f, 3.402823466e38f);
+}
+
+// Tiled copy of one problem's speeds (impassable outside its grid) and the
+// problem index of each of its tiles.
 template <int E, typename FT> __global__ void __launch_bounds__(STAGE_THREADS) k_tile_speed(Params P, Inst I, uint32_t j)
 {
     using S = Stage<E, FT>;
@@ -1842,7 +1839,7 @@ template <int E, typename FT> __global__ void __launch_bounds__(STAGE_THREADS) k
             for (int q = 0; q < STAGE_BATCH; q++) {
                 const int idx = (int)threadIdx.x + (q0 + q) * STAGE_THREADS;
                 const int r = idx / W, c = idx - r * W;
-                if (q0 + q < NL) buf[(c / E) * TS + r * E + c % E] = v[q];
+                if (q0 + q < NL) buf[(c / E) * TS + r * E + c % E] = tiled_speed(v[q], I.h);
             }
         }
         __syncthreads();
