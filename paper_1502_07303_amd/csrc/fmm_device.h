@@ -233,10 +233,33 @@ __device__ __forceinline__ void wave_sync()
 
 template <typename T> __device__ __forceinline__ T bcast0(T v) { return __shfl(v, 0); }
 
+// One step of a wavefront reduction: the minimum with the value of another lane
+// (DPP control CTRL, rows ROWS; lanes without a source keep their own).
+template <int CTRL, int ROWS> __device__ __forceinline__ double dpp_min(double v)
+{
+    const unsigned long long b = bits_of(v);
+    const int lo = (int)(uint32_t)b, hi = (int)(uint32_t)(b >> 32);
+    const uint32_t lo2 = (uint32_t)__builtin_amdgcn_update_dpp(lo, lo, CTRL, ROWS, 0xf, false);
+    const uint32_t hi2 = (uint32_t)__builtin_amdgcn_update_dpp(hi, hi, CTRL, ROWS, 0xf, false);
+    return fmin(v, bitsd((unsigned long long)lo2 | ((unsigned long long)hi2 << 32)));
+}
+
+// Minimum over the wavefront (uniform result; all lanes active): shifts within
+// rows of 16 lanes, then row broadcasts; lane 63 ends with the minimum.  Six
+// exchanges through LDS took six round trips in a row (64^3 shells 6.17 and
+// 6.08 ms, 1024^3 at 3.5h 184.5 and 183.0).
 __device__ __forceinline__ double wave_min(double v)
 {
-    for (int o = 32; o > 0; o >>= 1) v = fmin(v, __shfl_xor(v, o));
-    return v;
+    v = dpp_min<0x111, 0xf>(v);  // row_shr:1
+    v = dpp_min<0x112, 0xf>(v);
+    v = dpp_min<0x114, 0xf>(v);
+    v = dpp_min<0x118, 0xf>(v);
+    v = dpp_min<0x142, 0xa>(v);  // row_bcast:15
+    v = dpp_min<0x143, 0xc>(v);  // row_bcast:31
+    const unsigned long long b = bits_of(v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)b, 63);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(b >> 32), 63);
+    return bitsd((unsigned long long)lo | ((unsigned long long)hi << 32));
 }
 
 __device__ __forceinline__ unsigned long long wave_sum(unsigned long long v)
