@@ -33,6 +33,9 @@ struct Inst {
     const int64_t *seed_idx;
     const double *seed_val;
     int64_t n_seeds;
+    // the problem's first work unit of the speed copy and of finalize and its
+    // first seed, counted over the batch
+    int64_t unit_s, unit_f, seed0;
 };
 
 // Per-problem restart state (Alg. 16 runs once per problem: its own minimum,
