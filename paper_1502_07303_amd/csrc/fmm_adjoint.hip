@@ -526,8 +526,11 @@ struct AdjTileWave {
 // Bits 0 to 3 of m as 0/1 in the four bytes of a word.
 __device__ __forceinline__ uint32_t spread4(uint32_t m) { return ((m & 15u) * 0x00204081u) & 0x01010101u; }
 
-// a / S, correctly rounded for ordinary S: a refined reciprocal, the quotient
-// and a remainder step.  Extreme S or a take the division itself.
+// a / S, correctly rounded for ordinary operands: a refined reciprocal, the
+// quotient and a remainder step (the library's sequence without its scaling).
+// Where a step overflows or a value is infinite the quotient comes out infinite
+// or NaN (subnormal where the scaling would have mattered), and the division
+// itself is taken.
 __device__ __forceinline__ double adj_div(double a, double S)
 {
     double y = __builtin_amdgcn_rcp(S);
@@ -535,9 +538,8 @@ __device__ __forceinline__ double adj_div(double a, double S)
     y = __builtin_fma(y, __builtin_fma(-S, y, 1.0), y);
     double q = a * y;
     q = __builtin_fma(__builtin_fma(-q, S, a), y, q);
-    // the quotient and the remainder stay normal (a = 0 is exact)
-    const double m = fabs(a);
-    if (__builtin_expect(!(S > 0x1p-300 && S < 0x1p300 && (m == 0.0 || (m > 0x1p-600 && m < 0x1p600))), 0)) {
+    // signalling and quiet NaN, both infinities, both subnormals
+    if (__builtin_expect(__builtin_amdgcn_class(q, 0x1 | 0x2 | 0x4 | 0x10 | 0x80 | 0x200), 0)) {
         asm volatile("");
         q = a / S;
     }
