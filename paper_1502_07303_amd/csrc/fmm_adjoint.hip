@@ -529,8 +529,8 @@ __device__ __forceinline__ uint32_t spread4(uint32_t m) { return ((m & 15u) * 0x
 // a / S, correctly rounded for ordinary operands: a refined reciprocal, the
 // quotient and a remainder step (the library's sequence without its scaling).
 // Where a step overflows or a value is infinite the quotient comes out infinite
-// or NaN (subnormal where the scaling would have mattered), and the division
-// itself is taken.
+// or NaN, and where it underflows subnormal; below 2^-960 the remainder itself
+// may underflow.  There the division itself is taken.
 __device__ __forceinline__ double adj_div(double a, double S)
 {
     double y = __builtin_amdgcn_rcp(S);
@@ -539,7 +539,8 @@ __device__ __forceinline__ double adj_div(double a, double S)
     double q = a * y;
     q = __builtin_fma(__builtin_fma(-q, S, a), y, q);
     // signalling and quiet NaN, both infinities, both subnormals
-    if (__builtin_expect(__builtin_amdgcn_class(q, 0x1 | 0x2 | 0x4 | 0x10 | 0x80 | 0x200), 0)) {
+    const bool odd = __builtin_amdgcn_class(q, 0x1 | 0x2 | 0x4 | 0x10 | 0x80 | 0x200);
+    if (__builtin_expect((int)odd | ((int)(fabs(a) < 0x1p-960) & (int)(a != 0.0)), 0)) {
         asm volatile("");
         q = a / S;
     }

@@ -126,3 +126,24 @@ def test_adjoint_special_gradients(fmm, oracle_mod):
     assert np.array_equal(np.isinf(out), np.isinf(ref))
     fin = np.isfinite(ref)
     assert np.max(np.abs(out[fin] - ref[fin])) <= 1e-12 * np.max(np.abs(ref[fin]))
+
+
+@pytest.mark.parametrize("k", [-1000, -960, -600, 600, 980])
+def test_adjoint_extreme_gradients(fmm, oracle_mod, k):
+    """A gradient times 2^k gives the adjoint times 2^k: the sweep's division
+    without scaling hands over where its steps would under- or overflow.  Bar:
+    the suite's 1e-12, point by point where the result is well above the
+    subnormals (there the sums round as they do unscaled)."""
+    dev = torch.device("cuda:0")
+    F, h, T, st = solved(oracle_mod, (17, 9, 10), 3, torch.float64)
+    g = np.random.default_rng(4).normal(size=F.shape)
+    out = []
+    for s in (0, k):
+        gF = torch.empty(F.shape, dtype=torch.float64, device=dev)
+        fmm.AdjointSolver([{"F": torch.from_numpy(F).to(dev), "h": h, "T": torch.from_numpy(T).to(dev),
+                            "status": torch.from_numpy(st).to(dev), "dL_dT": torch.from_numpy(np.ldexp(g, s)).to(dev),
+                            "dL_dF": gF}]).run()
+        out.append(gF.cpu().numpy())
+    well = np.abs(out[0]) > 1e-5 * np.max(np.abs(out[0]))
+    assert well.sum() > F.size // 2
+    assert np.all(np.abs(np.ldexp(out[1][well], -k) - out[0][well]) <= 1e-12 * np.abs(out[0][well]))
