@@ -4,8 +4,10 @@
 #include <math.h>
 #include <string.h>
 
+#include <algorithm>
 #include <mutex>
 #include <unordered_map>
+#include <utility>
 #include <vector>
 
 #include "../../include/fmm.h"
@@ -524,6 +526,25 @@ static bool adj_tiled(int64_t n, const fmm_adjoint_problem *q)
     return true;
 }
 
+// The tile sweep's gather reads F while it writes dL_dF (the level sweep has read
+// all inputs by then): is some dL_dF laid over some F?
+static bool adj_output_over_F(int64_t n, const fmm_adjoint_problem *q, size_t f_size)
+{
+    std::vector<std::pair<const char *, const char *>> out;  // [first, last) of the outputs
+    for (int64_t i = 0; i < n; i++) {
+        const char *b = (const char *)q[i].dL_dF;
+        out.emplace_back(b, b + 8 * (size_t)(q[i].n0 * q[i].n1 * q[i].n2));
+    }
+    std::sort(out.begin(), out.end());  // equal or disjoint, so the ends are in order as well
+    for (int64_t i = 0; i < n; i++) {
+        const char *b = (const char *)q[i].F, *e = b + f_size * (size_t)(q[i].n0 * q[i].n1 * q[i].n2);
+        auto it = std::lower_bound(out.begin(), out.end(), b,
+                                   [](const std::pair<const char *, const char *> &o, const char *x) { return o.second <= x; });
+        if (it != out.end() && it->first < e) return true;
+    }
+    return false;
+}
+
 // Points and 8^3 tiles of a batch; its problem descriptors (nullable).
 static void adj_sizes(int64_t n, const fmm_adjoint_problem *q, std::vector<AdjInst> *insts, uint64_t *points,
                       uint64_t *tiles)
@@ -592,9 +613,13 @@ int fmm_adjoint_batch(int64_t n_problems, const fmm_adjoint_problem *problems, f
     uint64_t total = 0, nt = 0;
     adj_sizes(n_problems, problems, &insts, &total, &nt);
     if (total >= (1ull << 40)) return FMM_EINVAL;
-    if (adj_tiled(n_problems, problems)) {
+    // a workspace that holds the level sweep's arrays only (29 bytes per point)
+    // is served by that, and so is a gradient written over a model: the same
+    // system, solved more slowly.  (The tiles' arrays include the level sweep's
+    // room: 36 bytes per point rounded up, against 29.)
+    if (adj_tiled(n_problems, problems) && workspace_bytes >= adj_tile_layout(n_problems, nt).total &&
+        !adj_output_over_F(n_problems, problems, F_dtype == FMM_F64 ? 8 : 4)) {
         const AdjTileLayout L = adj_tile_layout(n_problems, nt);
-        if (workspace_bytes < L.total) return FMM_ENOMEM;
         char *b = (char *)workspace;
         AdjTileParams P;
         P.ctrl = (AdjCtrl *)(b + L.off_ctrl);

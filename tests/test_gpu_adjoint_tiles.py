@@ -147,3 +147,51 @@ def test_adjoint_extreme_gradients(fmm, oracle_mod, k):
     well = np.abs(out[0]) > 1e-5 * np.max(np.abs(out[0]))
     assert well.sum() > F.size // 2
     assert np.all(np.abs(np.ldexp(out[1][well], -k) - out[0][well]) <= 1e-12 * np.abs(out[0][well]))
+
+
+@pytest.mark.parametrize("dtype,scale", [(torch.float64, None), (torch.float32, (1.0, 1.7, 0.6))])
+def test_adjoint_in_the_level_sweeps_workspace(fmm, oracle_mod, dtype, scale):
+    """A workspace too small for the tiles but not for the level sweep is taken
+    (the level sweep solves it: same levels, the suite's bar), one below is not."""
+    dev = torch.device("cuda:0")
+    F, h, T, st = solved(oracle_mod, (17, 9, 10), 5, dtype, scale)
+    g = np.random.default_rng(6).normal(size=F.shape)
+    ref, levels = reference(F, h, T, st, g, scale)
+    for nbytes, ok in ((lambda full: full - 1, True), (lambda full: 30 * F.size + 8192, True),
+                       (lambda full: 28 * F.size, False)):
+        gF = torch.empty(F.shape, dtype=torch.float64, device=dev)
+        a = fmm.AdjointSolver([{"F": torch.from_numpy(F).to(dev), "h": h, "T": torch.from_numpy(T).to(dev),
+                                "status": torch.from_numpy(st).to(dev), "dL_dT": torch.from_numpy(g).to(dev),
+                                "dL_dF": gF, "axis_scale": scale}])
+        a.nbytes = nbytes(a.nbytes)
+        if not ok:
+            with pytest.raises(fmm.FmmError):
+                a.run()
+            continue
+        a.run()
+        assert a.stats().n_levels == levels
+        assert np.max(np.abs(gF.cpu().numpy() - ref)) <= 1e-12 * np.max(np.abs(ref))
+
+
+def test_adjoint_written_over_the_model(fmm, oracle_mod):
+    """dL_dF may be the memory of an F, of its own problem or of another (every
+    input is read before an output is written).  Bar: the suite's 1e-12."""
+    dev = torch.device("cuda:0")
+    qs, refs = [], []
+    for seed in (1, 2):
+        F, h, T, st = solved(oracle_mod, (17, 9, 10), seed, torch.float64)
+        g = np.random.default_rng(seed).normal(size=F.shape)
+        refs.append(reference(F, h, T, st, g)[0])
+        qs.append({"F": torch.from_numpy(F).to(dev), "h": h, "T": torch.from_numpy(T).to(dev),
+                   "status": torch.from_numpy(st).to(dev), "dL_dT": torch.from_numpy(g).to(dev)})
+    models = [q["F"].clone() for q in qs]
+    for own in (True, False):
+        for q, m in zip(qs, models):
+            q["F"].copy_(m)
+        for k in range(2):
+            qs[k]["dL_dF"] = qs[k if own else 1 - k]["F"]
+        a = fmm.AdjointSolver(qs)
+        a.run()
+        a.stats()
+        for q, ref in zip(qs, refs):
+            assert np.max(np.abs(q["dL_dF"].cpu().numpy() - ref)) <= 1e-12 * np.max(np.abs(ref)), own
