@@ -45,11 +45,15 @@ constexpr uint64_t ADJ_LOCAL_MASK = (1ull << 40) - 1;  // item = problem << 40 |
 
 // The neighbours a point's root uses: a and pick hold per axis the smaller
 // upwind value (+inf: none) and which neighbour it is (1 minus, 2 plus).
-// Returns 2 bits per axis.
+// Returns 2 bits per axis.  AN: some problem may have spacing factors.
+template <bool AN = true>
 __device__ __forceinline__ uint32_t upwind_pick(const Spacing &sp, const double a[3], const uint32_t pick[3], double r)
 {
     int k = 0;
-    (void)local_solve(sp, a[0], a[1], a[2], r, &k);
+    if constexpr (AN)
+        (void)local_solve(sp, a[0], a[1], a[2], r, &k);
+    else
+        (void)godunov_sel(a[0], a[1], a[2], r, &k);
     // the k smallest per-axis values, ties in axis order
     uint32_t code = 0;
 #pragma unroll
@@ -374,8 +378,10 @@ __device__ __forceinline__ uint32_t adj_tile_inst(const AdjTileParams &P, uint32
 
 // Setup, one wavefront per tile: |T| and status of the tile and its face
 // halo in LDS, the upwind set of every cell, and the tile's initial state.
+// AN as in the sweep: without the weighted solver beside it the uniform one's
+// registers do not spill (20 of them did; 256^3, 16 shots: 44.5 and 43.7 ms in all).
 constexpr int ADJT_SETUP_WAVES = 4;
-template <typename FT>
+template <typename FT, bool AN>
 __global__ void __launch_bounds__(ADJT_SETUP_WAVES * 64) __attribute__((amdgpu_waves_per_eu(4))) k_adjt_setup(AdjTileParams P)
 {
     constexpr int D = 10, OX = 100, OY = 10, OZ = 1;
@@ -437,9 +443,9 @@ __global__ void __launch_bounds__(ADJT_SETUP_WAVES * 64) __attribute__((amdgpu_w
             S[d] = (uint8_t)sh[f];
         }
         wave_sync();
-        const double w[3] = {I.sp.aniso ? 1.0 / (I.sp.s[0] * I.sp.s[0]) : 1.0,
-                             I.sp.aniso ? 1.0 / (I.sp.s[1] * I.sp.s[1]) : 1.0,
-                             I.sp.aniso ? 1.0 / (I.sp.s[2] * I.sp.s[2]) : 1.0};
+        const double w[3] = {AN && I.sp.aniso ? 1.0 / (I.sp.s[0] * I.sp.s[0]) : 1.0,
+                             AN && I.sp.aniso ? 1.0 / (I.sp.s[1] * I.sp.s[1]) : 1.0,
+                             AN && I.sp.aniso ? 1.0 / (I.sp.s[2] * I.sp.s[2]) : 1.0};
         uint64_t row = 0;
 #pragma unroll 1
         for (int x = 0; x < 8; x++) {
@@ -470,7 +476,7 @@ __global__ void __launch_bounds__(ADJT_SETUP_WAVES * 64) __attribute__((amdgpu_w
                             pick[ax] = 2;
                         }
                     }
-                    code = upwind_pick(I.sp, v, pick, I.h / f);
+                    code = upwind_pick<AN>(I.sp, v, pick, fast_div(I.h, f));
                     if (code) g = (tp < 0.0 ? -1.0 : 1.0) * gp;
                 }
             }
@@ -525,27 +531,6 @@ struct AdjTileWave {
 
 // Bits 0 to 3 of m as 0/1 in the four bytes of a word.
 __device__ __forceinline__ uint32_t spread4(uint32_t m) { return ((m & 15u) * 0x00204081u) & 0x01010101u; }
-
-// a / S, correctly rounded for ordinary operands: a refined reciprocal, the
-// quotient and a remainder step (the library's sequence without its scaling).
-// Where a step overflows or a value is infinite the quotient comes out infinite
-// or NaN, and where it underflows subnormal; below 2^-960 the remainder itself
-// may underflow.  There the division itself is taken.
-__device__ __forceinline__ double adj_div(double a, double S)
-{
-    double y = __builtin_amdgcn_rcp(S);
-    y = __builtin_fma(y, __builtin_fma(-S, y, 1.0), y);
-    y = __builtin_fma(y, __builtin_fma(-S, y, 1.0), y);
-    double q = a * y;
-    q = __builtin_fma(__builtin_fma(-q, S, a), y, q);
-    // signalling and quiet NaN, both infinities, both subnormals
-    const bool odd = __builtin_amdgcn_class(q, 0x1 | 0x2 | 0x4 | 0x10 | 0x80 | 0x200);
-    if (__builtin_expect((int)odd | ((int)(fabs(a) < 0x1p-960) & (int)(a != 0.0)), 0)) {
-        asm volatile("");
-        q = a / S;
-    }
-    return q;
-}
 
 // One activation of tile t: solve every cell whose dependents are solved.
 // AN: some problem of the batch has per-axis spacing.
@@ -747,7 +732,7 @@ __device__ __forceinline__ void adj_tile(const AdjTileParams &P, AdjTileLds &L, 
                 const double dif = AN ? w[ax] * (uq - v[ax]) : uq - v[ax];
                 d[ax] = (cross >> (2 * ax)) & 3u ? v[ax] : dif;
             }
-            const double c = adj_div(lt, (d[0] + d[1]) + d[2]);
+            const double c = fast_div(lt, (d[0] + d[1]) + d[2]);
             L.c[q] = c;
 #pragma unroll
             for (int ax = 0; ax < 3; ax++) {
@@ -1099,10 +1084,13 @@ template <typename FT> static hipError_t launch_adjoint_tiles_t(const AdjTilePar
     }
     const unsigned sb = (unsigned)std::min<int64_t>(((int64_t)P.ntiles + ADJT_SETUP_WAVES - 1) / ADJT_SETUP_WAVES,
                                                     (int64_t)cus * 16);
-    hipLaunchKernelGGL(k_adjt_setup<FT>, dim3(sb), dim3(ADJT_SETUP_WAVES * 64), 0, s, P);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
     bool aniso = false;
     for (int64_t j = 0; j < n; j++) aniso |= insts[j].sp.aniso != 0;
+    if (aniso)
+        hipLaunchKernelGGL((k_adjt_setup<FT, true>), dim3(sb), dim3(ADJT_SETUP_WAVES * 64), 0, s, P);
+    else
+        hipLaunchKernelGGL((k_adjt_setup<FT, false>), dim3(sb), dim3(ADJT_SETUP_WAVES * 64), 0, s, P);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
     if ((e = aniso ? launch_sweep<true>(P, s) : launch_sweep<false>(P, s)) != hipSuccess) return e;
     // gather each output array over the problems that share it
     std::vector<bool> done((size_t)n, false);

@@ -71,6 +71,28 @@ __device__ __forceinline__ double solver_div(double h, double f)
     return __builtin_fma(__builtin_fma(-f, q, h), y, q);
 }
 
+// a / S, correctly rounded for ordinary operands: a refined reciprocal, the
+// quotient and a remainder step (the library's sequence without its scaling).
+// Where a step overflows or a value is infinite the quotient comes out infinite
+// or NaN, and where it underflows subnormal; below 2^-960 the remainder itself
+// may underflow.  There the division itself is taken, unless the caller has no
+// use for the result (ok false).
+__device__ __forceinline__ double fast_div(double a, double S, bool ok = true)
+{
+    double y = __builtin_amdgcn_rcp(S);
+    y = __builtin_fma(y, __builtin_fma(-S, y, 1.0), y);
+    y = __builtin_fma(y, __builtin_fma(-S, y, 1.0), y);
+    double q = a * y;
+    q = __builtin_fma(__builtin_fma(-q, S, a), y, q);
+    // signalling and quiet NaN, both infinities, both subnormals
+    const bool odd = __builtin_amdgcn_class(q, 0x1 | 0x2 | 0x4 | 0x10 | 0x80 | 0x200);
+    if (__builtin_expect((int)ok & ((int)odd | ((int)(fabs(a) < 0x1p-960) & (int)(a != 0.0))), 0)) {
+        asm volatile("");
+        q = a / S;
+    }
+    return q;
+}
+
 // ---------------------------------------------------------------------------
 // Local solver (Alg. 11 with Eqs. 4-7).  a = per-axis upwind values (+inf when
 // an axis has no upwind neighbour), r = h / F.  With a1 <= a2 <= a3:
@@ -164,46 +186,61 @@ __device__ __forceinline__ double godunov(double x, double y, double z, double r
 //   u3 = (((w1 a1 + w2 a2) + w3 a3) + sqrt(((w1+w2)+w3) r^2
 //          - (((w1 w2)(a2-a1)^2 + (w1 w3)(a3-a1)^2) + (w2 w3)(a3-a2)^2))) / ((w1+w2)+w3)
 // with the same causality rule and minimum.  With unit scales every
-// operation is the one of godunov_sel().
+// operation is the one of godunov_sel().  Both roots are formed without a
+// branch, with the short root and quotient and the weights of the axes instead
+// of those of the sorted scales: the same operations, so the same bits (8e8
+// random arguments, scales and r over all exponents among them).  A march is
+// bound by its instructions, and this took five divisions and two roots of the
+// library: 101x87x118, 3 spacings, 6.49 -> 5.81 ms.
 __device__ __forceinline__ double godunov_w_sel(double x, double y, double z, double sx, double sy, double sz,
                                                 double r, int *k)
 {
-    double a1 = x, a2 = y, a3 = z, s1 = sx, s2 = sy, s3 = sz, t;
-    if (a1 > a2) { t = a1; a1 = a2; a2 = t; t = s1; s1 = s2; s2 = t; }
-    if (a2 > a3) {
-        t = a2; a2 = a3; a3 = t; t = s2; s2 = s3; s3 = t;
-        if (a1 > a2) { t = a1; a1 = a2; a2 = t; t = s1; s1 = s2; s2 = t; }
-    }
-    const double w1 = 1.0 / (s1 * s1), w2 = 1.0 / (s2 * s2), w3 = 1.0 / (s3 * s3);
-    *k = 0;
-    if (!(a1 < FMM_INF)) return FMM_INF;
-    double r2 = r * r;
+    // the weights of the axes are the same for all points and leave the loop
+    double a1 = x, a2 = y, a3 = z, s1 = sx, s2 = sy, s3 = sz;
+    double w1 = 1.0 / (sx * sx), w2 = 1.0 / (sy * sy), w3 = 1.0 / (sz * sz);
+    auto order = [](double &a, double &b, double &s, double &t, double &w, double &v) {
+        const bool c = __builtin_unpredictable(a > b);
+        const double a0 = a, s0 = s, w0 = w;
+        a = c ? b : a;
+        b = c ? a0 : b;
+        s = c ? t : s;
+        t = c ? s0 : t;
+        w = c ? v : w;
+        v = c ? w0 : v;
+    };
+    order(a1, a2, s1, s2, w1, w2);
+    order(a2, a3, s2, s3, w2, w3);
+    order(a1, a2, s1, s2, w1, w2);
+    // (sum + sqrt(D)) / W for a finite D >= 0, NaN (which no comparison below
+    // takes) for another D: the library's results bit for bit
+    auto root = [](double sum, double D, double W) {
+        const bool ok = __builtin_amdgcn_class(D, 0x20 | 0x40 | 0x80 | 0x100);  // +-0, positive and finite
+        double q = solver_sqrt_normal(D);
+        if (__builtin_expect((int)ok & (int)(D < 0x1p-767), 0)) {
+            asm volatile("");
+            q = sqrt(D);
+        }
+        return fast_div(sum + q, W, ok);
+    };
+    const double r2 = r * r;
     double best = a1 + r * s1;
-    *k = 1;
-    if (a2 < FMM_INF) {
-        double d12 = a2 - a1;
-        double D2 = (w1 + w2) * r2 - (w1 * w2) * (d12 * d12);
-        if (D2 >= 0.0) {
-            double u2 = ((w1 * a1 + w2 * a2) + sqrt(D2)) / (w1 + w2);
-            if (u2 > a2 && u2 < best) {
-                best = u2;
-                *k = 2;
-            }
-        }
-        if (a3 < FMM_INF) {
-            double d13 = a3 - a1, d23 = a3 - a2;
-            double D3 = ((w1 + w2) + w3) * r2 -
-                        (((w1 * w2) * (d12 * d12) + (w1 * w3) * (d13 * d13)) + (w2 * w3) * (d23 * d23));
-            if (D3 >= 0.0) {
-                double u3 = (((w1 * a1 + w2 * a2) + w3 * a3) + sqrt(D3)) / ((w1 + w2) + w3);
-                if (u3 > a3 && u3 < best) {
-                    best = u3;
-                    *k = 3;
-                }
-            }
-        }
+    int n = 1;
+    const double d12 = a2 - a1, d13 = a3 - a1, d23 = a3 - a2;
+    const double q12 = (w1 * w2) * (d12 * d12), W2 = w1 + w2, W3 = W2 + w3, m2 = w1 * a1 + w2 * a2;
+    // an absent value (+inf) makes its D -inf or NaN
+    const double u2 = root(m2, W2 * r2 - q12, W2);
+    if (u2 > a2 && u2 < best) {
+        best = u2;
+        n = 2;
     }
-    return best;
+    const double u3 = root(m2 + w3 * a3, W3 * r2 - ((q12 + (w1 * w3) * (d13 * d13)) + (w2 * w3) * (d23 * d23)), W3);
+    if (u3 > a3 && u3 < best) {
+        best = u3;
+        n = 3;
+    }
+    const bool any = a1 < FMM_INF;
+    *k = any ? n : 0;
+    return any ? best : FMM_INF;
 }
 
 // Per-axis grid spacing factors of a solve (spacing h * s[a] along axis a).
@@ -214,7 +251,12 @@ struct Spacing {
 
 __device__ __forceinline__ double local_solve(const Spacing &sp, double x, double y, double z, double r, int *k)
 {
-    if (sp.aniso) return godunov_w_sel(x, y, z, sp.s[0], sp.s[1], sp.s[2], r, k);
+    if (sp.aniso) {
+        // opaque here, so that the weights are not formed ahead of the branch
+        double s0 = sp.s[0], s1 = sp.s[1], s2 = sp.s[2];
+        asm volatile("" : "+v"(s0), "+v"(s1), "+v"(s2));
+        return godunov_w_sel(x, y, z, s0, s1, s2, r, k);
+    }
     return godunov_sel(x, y, z, r, k);
 }
 
