@@ -537,27 +537,23 @@ __device__ __forceinline__ bool eval_point(const TileLds<E, FT, G> &L, const Spa
     bool neg = vp < 0.0;
     bool improved = false;
     // one local solve per side that has an upwind point (kept as a loop so
-    // the solver is emitted once).  Lanes of either side take their solve
-    // together, and a second one follows only if some cell has upwind points on
-    // both.  (A solve for each side in turn: 256^3 spheres 3.32 ms, now 3.24,
-    // 101x87x118 with spacings 5.80 and 5.76.)
-    const bool has_neg = fmin(am[0], fmin(am[1], am[2])) < FMM_INF;
-    double x = has_neg ? am[0] : ap3[0], y = has_neg ? am[1] : ap3[1], z = has_neg ? am[2] : ap3[2];
-    bool side_neg = has_neg;
+    // the solver is emitted once), by the one-root solver: 256^3 spheres 3.30
+    // ms, now 3.19.  Lanes of both sides solving together: 3.15 to 3.24, but one
+    // form made 1024^3 1 % slower, the other 301x256x333 FP64.
 #pragma unroll 1
-    while (__ballot(fmin(x, fmin(y, z)) < FMM_INF)) {
+    for (int side = 0; side < 2; side++) {
+        const double x = side == 0 ? am[0] : ap3[0];
+        const double y = side == 0 ? am[1] : ap3[1];
+        const double z = side == 0 ? am[2] : ap3[2];
+        if (!(fmin(x, fmin(y, z)) < FMM_INF)) continue;
         int kk;
         const double u = AN ? godunov_w_sel(x, y, z, sp.s[0], sp.s[1], sp.s[2], r, &kk) : godunov(x, y, z, r);
-        const bool take = u < best || (side_neg && u == best && !neg && best < FMM_INF);
+        const bool take = u < best || (side == 0 && u == best && !neg && best < FMM_INF);
         if (take) {
             best = u;
-            neg = side_neg;
+            neg = side == 0;
             improved = true;
         }
-        x = side_neg ? ap3[0] : FMM_INF;
-        y = side_neg ? ap3[1] : FMM_INF;
-        z = side_neg ? ap3[2] : FMM_INF;
-        side_neg = false;
     }
     out = neg ? -best : best;
     return improved;
