@@ -1821,10 +1821,8 @@ __device__ __forceinline__ double tiled_speed(double f, double h) { return f > 0
 // largest finite one: the march's division wants a finite divisor, and h /
 // FLT_MAX is below the rounding of any value it is added to unless that value
 // is itself below about 1e-26.
-__device__ __forceinline__ float tiled_speed(float f, double)
-{
-    return __builtin_amdgcn_fmed3f(f, 0.0f, 3.402823466e38f);
-}
+// (A compare, not the median of three: that passes a signalling NaN as a speed.)
+__device__ __forceinline__ float tiled_speed(float f, double) { return f > 0.0f ? fminf(f, 3.402823466e38f) : 0.0f; }
 
 // Tiled copy of one problem's speeds (impassable outside its grid) and the
 // problem index of each of its tiles.
