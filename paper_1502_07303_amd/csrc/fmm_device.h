@@ -139,7 +139,7 @@ __device__ __forceinline__ double godunov_sel(double x, double y, double z, doub
     return best;
 }
 
-// The same root with one square root.  In exact arithmetic the candidate of k
+// The same root for r >= 0 with one square root.  In exact arithmetic the candidate of k
 // values is causal iff the sum of (a_k - a_i)^2 over them is below r^2, and
 // more values give a smaller root, so the sums decide which root to form.
 // Rounding can decide otherwise only where a sum is close to r^2: the two roots

@@ -38,8 +38,13 @@ namespace fmm {
 __global__ void k_eval_godunov(const double *__restrict__ a, const double *__restrict__ r,
                                double *__restrict__ out, int64_t n)
 {
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-        out[i] = godunov(a[3 * i], a[3 * i + 1], a[3 * i + 2], r[i]);
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
+        // a caller's r may be negative (a march's is not): the first root is the
+        // smallest then, where the one-root solver, which squares r, takes another
+        const double x = a[3 * i], y = a[3 * i + 1], z = a[3 * i + 2], ri = r[i];
+        int k;
+        out[i] = ri < 0.0 ? godunov_sel(x, y, z, ri, &k) : godunov(x, y, z, ri);
+    }
 }
 
 // ---------------------------------------------------------------------------
