@@ -183,7 +183,6 @@ Inst make_inst(const fmm_problem &q, int E, uint32_t base, const fmm_opts &o)
     I.t1 = t[1];
     I.t2 = t[2];
     I.base = base;
-    I.ntiles = (uint32_t)nt;
     I.h = q.h;
     I.stride = stride_of(o, q.h);
     I.F = q.F;

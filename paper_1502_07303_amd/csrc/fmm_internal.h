@@ -19,24 +19,28 @@ struct alignas(128) Slot {
 };
 
 // One problem of a batch: its grid, its place in the tile numbering and its
-// caller buffers.  A single solve is a batch of one.
+// caller buffers.  A single solve is a batch of one.  Callers size workspaces by
+// it, so what a launch needs besides takes the room of what the device copy does
+// not need.
 struct Inst {
     int64_t n0, n1, n2;
     int32_t t0, t1, t2;  // tiles per axis
     uint32_t base;       // global index of the problem's first tile
-    uint32_t ntiles;
-    uint32_t pad;
+    // the problem's first work unit of the speed copy and of finalize, counted
+    // over the batch (a unit is a tile or more, so 32 bits hold them)
+    uint32_t unit_s, unit_f;
     double h, stride;
     const void *F;  // row-major speeds
     double *T;      // row-major output
     uint8_t *status;
     const int64_t *seed_idx;
     const double *seed_val;
-    int64_t n_seeds;
-    // the problem's first work unit of the speed copy and of finalize and its
-    // first seed, counted over the batch
-    int64_t unit_s, unit_f, seed0;
+    union {
+        int64_t n_seeds;  // host
+        int64_t seed0;    // device copy: the problem's first seed, counted over the batch
+    };
 };
+static_assert(sizeof(Inst) == 112, "part of the workspace layout");
 
 // Per-problem restart state (Alg. 16 runs once per problem: its own minimum,
 // bound, dirty count and exit test).  Restart r reads slot[r % 3] and

@@ -1753,7 +1753,7 @@ __global__ void k_set_inst(Inst *dst, InstPack pk)
 
 // The problem whose range of a batch-wide count holds x: M is the member with
 // the first number of each problem's range.
-template <int64_t Inst::*M> __device__ __forceinline__ uint32_t inst_of(const Params &P, int64_t x)
+template <auto M> __device__ __forceinline__ uint32_t inst_of(const Params &P, int64_t x)
 {
     uint32_t lo = 0, hi = P.n_inst;
     while (hi - lo > 1) {
@@ -2153,12 +2153,12 @@ template <int E> static hipError_t launch_prepare_t(const Params &P, const Inst 
         pk.n = (uint32_t)std::min<int64_t>(INST_PACK, n - first);
         for (uint32_t k = 0; k < pk.n; k++) {
             Inst I = insts[first + k];
-            I.unit_s = units;
-            I.unit_f = unit_f;
+            I.unit_s = (uint32_t)units;
+            I.unit_f = (uint32_t)unit_f;
             I.seed0 = seeds;
             units += (int64_t)I.t0 * I.t1 * ((I.t2 + chs - 1) / chs);
             unit_f += (int64_t)I.t0 * I.t1 * ((I.t2 + chf - 1) / chf);
-            seeds += std::max<int64_t>(I.n_seeds, 0);
+            seeds += insts[first + k].n_seeds;
             pk.v[k] = I;
         }
         if (first == 0) {
