@@ -15,8 +15,6 @@ namespace fmm {
 struct AdjInst {
     int64_t n0, n1, n2;
     int64_t base;  // global index of the problem's first point in the level sweep's arrays
-    int32_t t0, t1, t2;  // 8^3 tiles per axis (tile sweep)
-    uint32_t tbase;      // global index of the problem's first tile (tile sweep)
     double h;
     const void *F;
     const double *T;
@@ -24,6 +22,12 @@ struct AdjInst {
     const double *dL_dT;
     double *dL_dF;
     Spacing sp;  // per-axis spacing factors (weights 1 / s^2)
+};
+
+// The same for the tile sweep.
+struct AdjTileInst : AdjInst {
+    int32_t t0, t1, t2;  // 8^3 tiles per axis
+    uint32_t tbase;      // global index of the problem's first tile
 };
 
 enum : uint32_t { ADJ_ERR_BARRIER = 32u };
@@ -39,10 +43,16 @@ struct AdjCtrl {
     uint32_t magic;                   // ADJ_MAGIC once a run has initialised the workspace
     alignas(128) unsigned long long len[3];  // frontier lengths, by level mod 3
     alignas(128) unsigned long long n_points;  // points of the linear system
-    // tile sweep: claim counters of the phases (by phase mod 3), one per
-    // segment of the work list and 128 B apart
+};
+
+// The tile sweep's adds claim counters of the phases (by phase mod 3), one per
+// segment of the work list and 128 B apart.
+struct AdjTileCtrl : AdjCtrl {
     alignas(128) uint32_t work[3][8][32];
 };
+
+// Callers size workspaces by the level sweep's structures.
+static_assert(sizeof(AdjCtrl) == 512 && sizeof(AdjInst) == 112, "part of the workspace layout");
 
 struct AdjParams {
     AdjCtrl *ctrl;
@@ -58,8 +68,8 @@ struct AdjParams {
 // neighbour on axis 0, 1, 2 is the minus (even bytes) or plus (odd bytes) one,
 // byte 6 the cells that are solved and byte 7 the cells of the linear system.
 struct AdjTileParams {
-    AdjCtrl *ctrl;
-    const AdjInst *inst;
+    AdjTileCtrl *ctrl;
+    const AdjTileInst *inst;
     uint32_t n_inst, ntiles;
     // 16 words per tile: tile strides along axes 0 and 1, flags (bits 0 to 5:
     // there is a tile across face f; bit 6: per-axis spacing), problem, and per
@@ -80,8 +90,8 @@ constexpr uint64_t ADJT_WAIT = ~0ull;
 constexpr uint32_t ADJT_NOLEV = ~0u;
 
 constexpr int ADJ_PACK = 16;
-struct AdjPack {
-    AdjInst v[ADJ_PACK];
+template <typename I> struct AdjPack {
+    I v[ADJ_PACK];
     uint32_t first, n;
 };
 
@@ -150,8 +160,8 @@ inline AdjTileLayout adj_tile_layout(int64_t n, uint64_t nt)
         o = adj_align(o + bytes);
         return at;
     };
-    L.off_ctrl = take(sizeof(AdjCtrl));
-    L.off_inst = take(sizeof(AdjInst) * (size_t)n);
+    L.off_ctrl = take(sizeof(AdjTileCtrl));
+    L.off_inst = take(sizeof(AdjTileInst) * (size_t)n);
     L.off_head = take(64 * nt);
     L.off_row = take(8 * 64 * nt);
     L.off_u = take(8 * 512 * nt);
@@ -167,7 +177,7 @@ inline AdjTileLayout adj_tile_layout(int64_t n, uint64_t nt)
     return L;
 }
 
-hipError_t launch_adjoint_tiles(const AdjTileParams &P, const AdjInst *insts, int64_t n, bool f64, hipStream_t s);
-hipError_t launch_adjoint(const AdjParams &P, const AdjInst *insts, int64_t n, bool f64, hipStream_t s);
+hipError_t launch_adjoint_tiles(const AdjTileParams &P, const AdjTileInst *insts, int64_t n, bool f64, hipStream_t s);
+hipError_t launch_adjoint(const AdjParams &P, const AdjTileInst *insts, int64_t n, bool f64, hipStream_t s);
 
 }  // namespace fmm

@@ -303,7 +303,7 @@ __global__ void k_adj_init(AdjParams P, uint32_t n_inst)
     }
 }
 
-__global__ void k_adj_set_inst(AdjInst *dst, AdjPack pk)
+__global__ void k_adj_set_inst(AdjInst *dst, AdjPack<AdjInst> pk)
 {
     const uint32_t k = threadIdx.x;
     if (k < pk.n) dst[pk.first + k] = pk.v[k];
@@ -394,7 +394,7 @@ __global__ void __launch_bounds__(ADJT_SETUP_WAVES * 64) __attribute__((amdgpu_w
     unsigned long long mine = 0;
     for (uint32_t t = blockIdx.x * ADJT_SETUP_WAVES + wid; t < P.ntiles; t += gridDim.x * ADJT_SETUP_WAVES) {
         const uint32_t j = __builtin_amdgcn_readfirstlane(P.n_inst == 1 ? 0u : adj_tile_inst(P, t));
-        const AdjInst &I = P.inst[j];
+        const AdjTileInst &I = P.inst[j];
         const uint32_t tl = t - I.tbase;
         const int64_t z0 = (int64_t)(tl % (uint32_t)I.t2) * 8;
         const int64_t y0 = (int64_t)((tl / (uint32_t)I.t2) % (uint32_t)I.t1) * 8;
@@ -835,7 +835,7 @@ __global__ void __launch_bounds__(ADJT_NW * 64) __attribute__((amdgpu_waves_per_
     __shared__ AdjTileLds s_tile[ADJT_NW];
     __shared__ uint32_t s_ok, s_drained, s_cnt[ADJT_NW];
     __shared__ unsigned long long s_base;
-    AdjCtrl *c = P.ctrl;
+    AdjTileCtrl *c = P.ctrl;
     const int lane = threadIdx.x & 63, wid = (int)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     AdjTileLds &L = s_tile[wid];
     const uint32_t nwg = gridDim.x, nseg = nwg < ADJT_SEGS ? nwg : ADJT_SEGS;
@@ -952,11 +952,11 @@ __global__ void __launch_bounds__(256) k_adjt_gather(AdjTileParams P, AdjTileGat
 }
 
 // The control block; with the first problem descriptors.
-__global__ void k_adjt_init(AdjTileParams P, AdjPack pk)
+__global__ void k_adjt_init(AdjTileParams P, AdjPack<AdjTileInst> pk)
 {
     const uint32_t k = threadIdx.x;
     if (pk.first == 0) {
-        AdjCtrl *c = P.ctrl;
+        AdjTileCtrl *c = P.ctrl;
         if (k == 0) {
             c->bar = 0;
             c->abort = 0;
@@ -970,10 +970,10 @@ __global__ void k_adjt_init(AdjTileParams P, AdjPack pk)
         }
         if (k < 3 * ADJT_SEGS) c->work[k / ADJT_SEGS][k % ADJT_SEGS][0] = 0;
     }
-    if (k < pk.n) ((AdjInst *)P.inst)[pk.first + k] = pk.v[k];
+    if (k < pk.n) ((AdjTileInst *)P.inst)[pk.first + k] = pk.v[k];
 }
 
-template <typename FT> static hipError_t launch_adjoint_t(const AdjParams &P, const AdjInst *insts, int64_t n,
+template <typename FT> static hipError_t launch_adjoint_t(const AdjParams &P, const AdjTileInst *insts, int64_t n,
                                                        hipStream_t s)
 {
     const int cus = adj_cus();
@@ -981,7 +981,7 @@ template <typename FT> static hipError_t launch_adjoint_t(const AdjParams &P, co
     hipLaunchKernelGGL(k_adj_init, dim3(1), dim3(64), 0, s, P, (uint32_t)n);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     for (int64_t first = 0; first < n; first += ADJ_PACK) {
-        AdjPack pk;
+        AdjPack<AdjInst> pk;
         memset(&pk, 0, sizeof pk);
         pk.first = (uint32_t)first;
         pk.n = (uint32_t)std::min<int64_t>(ADJ_PACK, n - first);
@@ -1044,7 +1044,7 @@ template <typename FT> static hipError_t launch_adjoint_t(const AdjParams &P, co
     return hipSuccess;
 }
 
-hipError_t launch_adjoint(const AdjParams &P, const AdjInst *insts, int64_t n, bool f64, hipStream_t s)
+hipError_t launch_adjoint(const AdjParams &P, const AdjTileInst *insts, int64_t n, bool f64, hipStream_t s)
 {
     return f64 ? launch_adjoint_t<double>(P, insts, n, s) : launch_adjoint_t<float>(P, insts, n, s);
 }
@@ -1068,13 +1068,13 @@ template <bool AN> static hipError_t launch_sweep(const AdjTileParams &P, hipStr
     return launch_coresident((const void *)kern, dim3(grid), dim3(ADJT_NW * 64), args, s);
 }
 
-template <typename FT> static hipError_t launch_adjoint_tiles_t(const AdjTileParams &P, const AdjInst *insts, int64_t n,
+template <typename FT> static hipError_t launch_adjoint_tiles_t(const AdjTileParams &P, const AdjTileInst *insts, int64_t n,
                                                                hipStream_t s)
 {
     const int cus = adj_cus();
     hipError_t e;
     for (int64_t first = 0; first < n; first += ADJ_PACK) {
-        AdjPack pk;
+        AdjPack<AdjTileInst> pk;
         memset(&pk, 0, sizeof pk);
         pk.first = (uint32_t)first;
         pk.n = (uint32_t)std::min<int64_t>(ADJ_PACK, n - first);
@@ -1096,7 +1096,7 @@ template <typename FT> static hipError_t launch_adjoint_tiles_t(const AdjTilePar
     std::vector<bool> done((size_t)n, false);
     for (int64_t j = 0; j < n; j++) {
         if (done[(size_t)j]) continue;
-        const AdjInst &J = insts[j];
+        const AdjTileInst &J = insts[j];
         AdjTileGather G;
         memset(&G, 0, sizeof G);
         G.out = J.dL_dF;
@@ -1127,7 +1127,7 @@ template <typename FT> static hipError_t launch_adjoint_tiles_t(const AdjTilePar
     return hipSuccess;
 }
 
-hipError_t launch_adjoint_tiles(const AdjTileParams &P, const AdjInst *insts, int64_t n, bool f64, hipStream_t s)
+hipError_t launch_adjoint_tiles(const AdjTileParams &P, const AdjTileInst *insts, int64_t n, bool f64, hipStream_t s)
 {
     return f64 ? launch_adjoint_tiles_t<double>(P, insts, n, s) : launch_adjoint_tiles_t<float>(P, insts, n, s);
 }

@@ -549,7 +549,7 @@ static bool adj_output_over_F(int64_t n, const fmm_adjoint_problem *q, size_t f_
 }
 
 // Points and 8^3 tiles of a batch; its problem descriptors (nullable).
-static void adj_sizes(int64_t n, const fmm_adjoint_problem *q, std::vector<AdjInst> *insts, uint64_t *points,
+static void adj_sizes(int64_t n, const fmm_adjoint_problem *q, std::vector<AdjTileInst> *insts, uint64_t *points,
                       uint64_t *tiles)
 {
     uint64_t total = 0, nt = 0;
@@ -558,7 +558,7 @@ static void adj_sizes(int64_t n, const fmm_adjoint_problem *q, std::vector<AdjIn
         uint64_t k = 0;
         tile_grid(q[i].n0, q[i].n1, q[i].n2, 8, t, &k);
         if (insts) {
-            AdjInst &I = (*insts)[(size_t)i];
+            AdjTileInst &I = (*insts)[(size_t)i];
             memset(&I, 0, sizeof I);
             I.n0 = q[i].n0;
             I.n1 = q[i].n1;
@@ -612,7 +612,7 @@ int fmm_adjoint_batch(int64_t n_problems, const fmm_adjoint_problem *problems, f
         const fmm_adjoint_problem &a = problems[it->second], &b = problems[i];
         if (a.n0 != b.n0 || a.n1 != b.n1 || a.n2 != b.n2) return FMM_EINVAL;
     }
-    std::vector<AdjInst> insts((size_t)n_problems);
+    std::vector<AdjTileInst> insts((size_t)n_problems);
     uint64_t total = 0, nt = 0;
     adj_sizes(n_problems, problems, &insts, &total, &nt);
     if (total >= (1ull << 40)) return FMM_EINVAL;
@@ -625,8 +625,8 @@ int fmm_adjoint_batch(int64_t n_problems, const fmm_adjoint_problem *problems, f
         const AdjTileLayout L = adj_tile_layout(n_problems, nt);
         char *b = (char *)workspace;
         AdjTileParams P;
-        P.ctrl = (AdjCtrl *)(b + L.off_ctrl);
-        P.inst = (const AdjInst *)(b + L.off_inst);
+        P.ctrl = (AdjTileCtrl *)(b + L.off_ctrl);
+        P.inst = (const AdjTileInst *)(b + L.off_inst);
         P.n_inst = (uint32_t)n_problems;
         P.ntiles = (uint32_t)nt;
         P.head = (uint32_t *)(b + L.off_head);

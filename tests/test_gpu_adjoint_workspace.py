@@ -1,0 +1,37 @@
+"""The smallest workspaces the adjoint takes (the level sweep's: 29 bytes per point,
+the descriptors and a control block) are pinned: callers that sized one once may
+pass it.  A byte less is refused.  Bar: 1e-12 of the largest gradient against the
+result with the reported workspace (the same system, summed in another order)."""
+import numpy as np
+import pytest
+import torch
+
+from paper_1502_07303_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("shape,n,nbytes", [((17, 9, 10), 1, 45312), ((40, 33, 52), 1, 1991680), ((9, 11, 8), 30, 693760)])
+def test_smallest_workspace(shape, n, nbytes):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1502_07303_amd import fmm
+    dev = torch.device("cuda:0")
+    w = inputs.random_small(shape, n_sources=2, seed=3, dtype=torch.float32)
+    F = w.F.to(dev)
+    T, st, _ = fmm.solve(F, w.h, w.seed_idx.to(dev), w.seed_val.to(dev))
+    rng = np.random.default_rng(1)
+    g = [torch.from_numpy(rng.normal(size=shape)).to(dev) for _ in range(n)]
+    got = []
+    for size in (None, nbytes, nbytes - 1):
+        gF = torch.empty(shape, dtype=torch.float64, device=dev)
+        a = fmm.AdjointSolver([{"F": F, "h": w.h, "T": T, "status": st, "dL_dT": g[k], "dL_dF": gF} for k in range(n)])
+        a.nbytes = size or a.nbytes
+        if size == nbytes - 1:
+            with pytest.raises(fmm.FmmError):
+                a.run()
+            continue
+        a.run()
+        a.stats()
+        got.append(gF)
+    assert float((got[0] - got[1]).abs().max()) <= 1e-12 * float(got[0].abs().max())
