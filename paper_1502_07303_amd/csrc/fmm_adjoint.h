@@ -72,13 +72,14 @@ struct AdjTileParams {
     const AdjTileInst *inst;
     uint32_t n_inst, ntiles;
     // 16 words per tile: tile strides along axes 0 and 1, flags (bits 0 to 5:
-    // there is a tile across face f; bit 6: per-axis spacing), problem, and per
-    // face 64 bits for the cells that wait for a contribution across it
+    // there is a tile across face f; bit 6: per-axis spacing; bit 7: some lambda
+    // is scaled), problem, and per face 64 bits for the cells that wait for a contribution across it
     uint32_t *head;
     uint64_t *row;    // 64 row words per tile
     double *u;        // |T|
     double *c;        // sign(T) dL/dT until the cell is solved, then lambda = lt / S
-    uint32_t *lev;    // dependency level of a solved cell (1: no dependents)
+    uint32_t *lev;    // dependency level of a solved cell (1: no dependents), or
+                      // ADJT_SCALED | (e + ADJT_BIAS): lambda is c 2^e
     // per tile and face (2 * axis + 1 for the + side), 64 cells of the face:
     double *fw;    // weighted difference to the upwind neighbour across the face (0: none)
     uint64_t *fo;  // contribution passed across it (ADJT_WAIT until the cell is solved, 0 bits: none)
@@ -88,6 +89,8 @@ struct AdjTileParams {
 };
 constexpr uint64_t ADJT_WAIT = ~0ull;
 constexpr uint32_t ADJT_NOLEV = ~0u;
+constexpr uint32_t ADJT_SCALED = 1u << 31;
+constexpr int ADJT_BIAS = 1 << 14;
 
 constexpr int ADJ_PACK = 16;
 template <typename I> struct AdjPack {

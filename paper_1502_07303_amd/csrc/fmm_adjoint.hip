@@ -106,6 +106,18 @@ __device__ __forceinline__ uint32_t upwind_code(const AdjInst &I, int64_t p, int
     return upwind_pick(I.sp, a, pick, I.h / f);
 }
 
+// dL/dF of a point with lt / S = lambda 2^e: -(h^2 / F^3) lambda 2^e, formed from
+// mantissas and exponents apart.  h^2 / F^3 leaves the range of doubles for speeds
+// beyond 1e+-102, though the gradient, about h lt / F^2, need not.
+__device__ __forceinline__ double adj_term(double h, double f, double lambda, int e)
+{
+    const double mf = __builtin_amdgcn_frexp_mant(f);
+    const double q = quick_div(__builtin_amdgcn_frexp_mant(h), mf);  // h / F
+    const int eq = __builtin_amdgcn_frexp_exp(h) - __builtin_amdgcn_frexp_exp(f);
+    const double m = fast_div(__builtin_amdgcn_frexp_mant(lambda) * q * q, mf);  // lambda may be infinite or NaN
+    return __builtin_amdgcn_ldexp(-m, __builtin_amdgcn_frexp_exp(lambda) + e + 2 * eq - __builtin_amdgcn_frexp_exp(f));
+}
+
 // Counter offset of points outside the linear system (see k_adj_setup).
 constexpr uint32_t ADJ_FIXED_COUNT = 1u << 30;
 
@@ -221,7 +233,8 @@ __device__ __forceinline__ void adj_point(const AdjParams &P, uint64_t it, bool 
         S += d[ax];
     }
     // this point's gradient term; its accumulator is not needed any more
-    P.acc[g] = -(I.h * I.h) / (f * f * f * S) * lt;
+    P.acc[g] = adj_term(I.h, f, __builtin_amdgcn_frexp_mant(lt) / __builtin_amdgcn_frexp_mant(S),
+                        __builtin_amdgcn_frexp_exp(lt) - __builtin_amdgcn_frexp_exp(S));
 #pragma unroll
     for (int ax = 0; ax < 3; ax++) {
         if (q[ax] < 0) continue;
@@ -732,12 +745,31 @@ __device__ __forceinline__ void adj_tile(const AdjTileParams &P, AdjTileLds &L, 
                 const double dif = AN ? w[ax] * (uq - v[ax]) : uq - v[ax];
                 d[ax] = (cross >> (2 * ax)) & 3u ? v[ax] : dif;
             }
-            const double c = fast_div(lt, (d[0] + d[1]) + d[2]);
+            // lambda = lt / S, and d lambda to each upwind cell.  Where lambda
+            // leaves the range of normal numbers (lt = 0 apart) the weights d / S
+            // are formed first, and lambda is kept as mantissa and exponent.
+            const double S = (d[0] + d[1]) + d[2];
+            double c = quick_div(lt, S);
+            double p[3] = {d[0] * c, d[1] * c, d[2] * c};
+            // signalling and quiet NaN; those, infinities, subnormals and zeros
+            const bool nan = __builtin_amdgcn_class(c, 0x1 | 0x2);
+            const bool odd = __builtin_amdgcn_class(c, 0x1 | 0x2 | 0x4 | 0x10 | 0x20 | 0x40 | 0x80 | 0x200);
+            // (below 2^-960 the quotient's remainder may underflow)
+            const int rare = (int)nan | (((int)odd | (int)(fabs(lt) < 0x1p-960)) & (int)(lt != 0.0));
+            if (__builtin_expect(rare, 0)) {
+                asm volatile("");
+#pragma unroll
+                for (int ax = 0; ax < 3; ax++) p[ax] = (d[ax] / S) * lt;
+                c = __builtin_amdgcn_frexp_mant(lt) / __builtin_amdgcn_frexp_mant(S);
+                const int e = __builtin_amdgcn_frexp_exp(lt) - __builtin_amdgcn_frexp_exp(S);
+                L.lev[q] = ADJT_SCALED | (uint32_t)(e + ADJT_BIAS);  // no longer read as a level
+                sent |= 64u;
+            }
             L.c[q] = c;
 #pragma unroll
             for (int ax = 0; ax < 3; ax++) {
                 if (!in[ax]) continue;
-                __hip_atomic_fetch_add(&L.c[tgt[ax]], d[ax] * c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+                __hip_atomic_fetch_add(&L.c[tgt[ax]], p[ax], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
                 __hip_atomic_fetch_max(&L.lev[tgt[ax]], lev, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
             }
             // the contributions come before the counters (LDS works in order)
@@ -757,7 +789,7 @@ __device__ __forceinline__ void adj_tile(const AdjTileParams &P, AdjTileLds &L, 
                     if (!c2) continue;
                     const uint32_t f = 2 * ax + (c2 >> 1);
                     const int at = ax == 0 ? q & 63 : ax == 1 ? qx * 8 + qz : q >> 3;
-                    uint64_t b = bits_of(d[ax] * c);
+                    uint64_t b = bits_of(p[ax]);
                     if (b == ADJT_WAIT) b = 0x7ff8000000000000ull;  // a NaN whose bits mean "waiting"
                     const size_t o = ((size_t)t * 6 + f) * 64 + at;
                     __hip_atomic_store(&P.fo[o], b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
@@ -790,6 +822,7 @@ __device__ __forceinline__ void adj_tile(const AdjTileParams &P, AdjTileLds &L, 
             want = true;
         }
     }
+    if (__ballot((sent >> 6) & 1u) != 0 && lane == 0) P.head[(size_t)t * 16 + 2] = flags | 128u;
     if (want) want = atomicExch(&P.tag[nb], phase + 1u) != phase + 1u;
     const unsigned long long m = __ballot(want);
     const uint32_t cnt = (uint32_t)__popcll(m);
@@ -935,14 +968,19 @@ __global__ void __launch_bounds__(256) k_adjt_gather(AdjTileParams P, AdjTileGat
         for (uint32_t k = 0; k < G.m; k++) {
             const size_t tk = (size_t)G.tbase[k] + t;
             const FT *F = (const FT *)G.F[k];
-            const double hh = -(G.h[k] * G.h[k]);
+            const bool scaled = (P.head[tk * 16 + 2] & 128u) != 0;
 #pragma unroll
             for (int x = 0; x < 8; x++) {
                 // the row word's system byte; inside the system the point is in the grid
                 const uint32_t sys = (uint32_t)(P.row[tk * 64 + x * 8 + a] >> 56);
                 if (!((sys >> b) & 1u)) continue;
                 const double f = (double)F[((x0 + x) * G.n1 + y0 + a) * G.n2 + z0 + b];
-                s[x] += hh / (f * f * f) * P.c[tk * 512 + x * 64 + lane];
+                int e = 0;
+                if (scaled) {
+                    const uint32_t l = P.lev[tk * 512 + x * 64 + lane];
+                    if (l & ADJT_SCALED) e = (int)(l & ~ADJT_SCALED) - ADJT_BIAS;
+                }
+                s[x] += adj_term(G.h[k], f, P.c[tk * 512 + x * 64 + lane], e);
             }
         }
 #pragma unroll

@@ -73,17 +73,22 @@ __device__ __forceinline__ double solver_div(double h, double f)
 
 // a / S, correctly rounded for ordinary operands: a refined reciprocal, the
 // quotient and a remainder step (the library's sequence without its scaling).
-// Where a step overflows or a value is infinite the quotient comes out infinite
+__device__ __forceinline__ double quick_div(double a, double S)
+{
+    double y = __builtin_amdgcn_rcp(S);
+    y = __builtin_fma(y, __builtin_fma(-S, y, 1.0), y);
+    y = __builtin_fma(y, __builtin_fma(-S, y, 1.0), y);
+    const double q = a * y;
+    return __builtin_fma(__builtin_fma(-q, S, a), y, q);
+}
+
+// The same for all operands.  Where a step overflows or a value is infinite the quotient comes out infinite
 // or NaN, and where it underflows subnormal; below 2^-960 the remainder itself
 // may underflow.  There the division itself is taken, unless the caller has no
 // use for the result (ok false).
 __device__ __forceinline__ double fast_div(double a, double S, bool ok = true)
 {
-    double y = __builtin_amdgcn_rcp(S);
-    y = __builtin_fma(y, __builtin_fma(-S, y, 1.0), y);
-    y = __builtin_fma(y, __builtin_fma(-S, y, 1.0), y);
-    double q = a * y;
-    q = __builtin_fma(__builtin_fma(-q, S, a), y, q);
+    double q = quick_div(a, S);
     // signalling and quiet NaN, both infinities, both subnormals
     const bool odd = __builtin_amdgcn_class(q, 0x1 | 0x2 | 0x4 | 0x10 | 0x80 | 0x200);
     if (__builtin_expect((int)ok & ((int)odd | ((int)(fabs(a) < 0x1p-960) & (int)(a != 0.0))), 0)) {

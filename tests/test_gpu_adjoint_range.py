@@ -1,0 +1,78 @@
+"""The adjoint where its intermediate quantities leave the range of doubles though
+its results do not: FP64 speeds of extreme magnitude, uniform or mixed in one
+grid, and gradients of extreme magnitude beside them, by both sweeps (the level
+sweep is taken where the workspace is a byte short of the tile sweep's).
+
+The reference is the oracle's upwind system solved in extended precision (64-bit
+mantissa, 15-bit exponent).  All dL/dT are >= 0, so nothing cancels and the bar
+holds point by point: fewer than 100 dependency levels, each of at most ten
+roundings, sum to less than 1e-12.  Points whose result or accumulated gradient is
+below 2^-960 are left out (sums of subnormals round absolutely)."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import adjoint as oadj
+
+pytestmark = pytest.mark.gpu
+
+LD = np.longdouble
+
+
+def reference(F, h, T, status, g, scale=None):
+    """(dL/dF, accumulated dL/du) in extended precision."""
+    assert np.finfo(LD).nmant >= 63
+    sets = oadj.upwind_sets(F, h, T, status, scale)
+    w = [LD(1)] * 3 if scale is None else [LD(1) / (LD(s) * LD(s)) for s in scale]
+    u, f = np.abs(T.reshape(-1)).astype(LD), F.reshape(-1).astype(LD)
+    lt = {p: LD(g.reshape(-1)[p]) for p, U in sets.items() if U}
+    out, acc = np.zeros(T.size, LD), np.zeros(T.size, LD)
+    for p in sorted(lt, key=lambda q: -u[q]):
+        S = sum((w[ax] * (u[p] - u[q]) for q, ax in sets[p]), LD(0))
+        out[p] = -((LD(h) / f[p]) / S) * (lt[p] * (LD(h) / f[p])) / f[p]
+        acc[p] = lt[p]
+        for q, ax in sets[p]:
+            if q in lt:
+                lt[q] += w[ax] * (u[p] - u[q]) / S * lt[p]
+    return out, acc
+
+
+@pytest.mark.parametrize("level", [False, True])
+@pytest.mark.parametrize("k,spread,gk,scale", [
+    (0, 0, 0, None), (-352, 0, 0, None), (-346, 0, 0, None), (338, 0, 0, None), (345, 0, 0, None), (-500, 0, 0, None),
+    (500, 0, 0, None), (1000, 0, 30, None), (-900, 0, -900, None), (300, 0, -900, None), (900, 0, 900, None),
+    (-350, 40, 0, None), (338, 40, 0, None), (0, 300, 0, None), (0, 0, -1000, None), (0, 0, 1000, None),
+    (-346, 0, 0, (1.0, 1.7, 0.6)), (345, 0, 0, (1.0, 1.7, 0.6)), (0, 300, 0, (1.0, 1.7, 0.6))])
+def test_adjoint_range(oracle_mod, level, k, spread, gk, scale):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1502_07303_amd import fmm
+    dev = torch.device("cuda:0")
+    shape, h = (11, 9, 17), 2.0 ** -4
+    rng = np.random.default_rng(9)
+    F = np.ldexp(rng.uniform(0.5, 2.0, shape), k)
+    if spread:
+        F = np.ldexp(F, rng.integers(-spread, spread + 1, shape))
+    idx, val = np.array([5 * 9 * 17 + 4 * 17 + 3]), np.zeros(1)
+    T, st, _, _ = oracle_mod.solve(F, h, idx, val, axis_scale=scale)
+    g = np.ldexp(rng.uniform(0.5, 1.0, shape), gk)
+    ref, acc = reference(F, h, T, st, g, scale)
+    gF = torch.empty(shape, dtype=torch.float64, device=dev)
+    a = fmm.AdjointSolver([{"F": torch.from_numpy(F).to(dev), "h": h, "T": torch.from_numpy(T).to(dev),
+                            "status": torch.from_numpy(st).to(dev), "dL_dT": torch.from_numpy(g).to(dev),
+                            "dL_dF": gF, "axis_scale": scale}])
+    if level:
+        a.nbytes -= 1
+    a.run()
+    a.stats()
+    got = gF.cpu().numpy().reshape(-1)
+    top = LD(np.finfo(np.float64).max)
+    over = np.abs(ref) > top * (1 + LD(2) ** -50)
+    well = (acc > LD(2) ** -960) & (np.abs(ref) > LD(2) ** -960) & (np.abs(ref) < top * (1 - LD(2) ** -30)) & (acc < top / 4)
+    assert not np.any(np.isnan(got))
+    assert np.all(np.isinf(got[over]))
+    err = np.abs(got[well].astype(LD) - ref[well]) / np.abs(ref[well])
+    assert err.size == 0 or np.max(err) <= 1e-12, float(np.max(err))
+    assert np.all(got[ref == 0] == 0)
+    zero = np.abs(ref) < LD(2) ** -1080
+    assert np.all(np.abs(got[zero]) < 2.0 ** -1060)
