@@ -309,10 +309,11 @@ typedef struct {
 } fmm_adjoint_stats;
 
 /* Device workspace for an adjoint batch (0 if invalid): about 36 bytes per
- * grid point of all problems, each axis rounded up to a multiple of 8; about
- * 29 bytes per point for a batch with a problem of fewer than 8 points along
- * an axis.  A smaller workspace of at least 29 bytes per point (and the
- * problems' descriptors) is accepted for any batch, at a lower speed. */
+ * grid point of all problems, each axis rounded up to a multiple of 8, or
+ * about 29 bytes per point where the rounding up multiplies the points by
+ * more than 6 (planes, lines).  A smaller workspace of at least 29 bytes per
+ * point (and the problems' descriptors) is accepted for any batch, at a lower
+ * speed. */
 size_t fmm_adjoint_workspace_bytes(int64_t n_problems, const fmm_adjoint_problem *problems);
 
 /* dL/dF of every problem of the batch (asynchronous on `stream`; each dL_dF

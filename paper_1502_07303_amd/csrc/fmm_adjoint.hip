@@ -22,14 +22,15 @@
 // solver as the forward march, so the same root and the same k) into 2 bits per
 // axis.  All problems of a batch are then solved by one persistent cooperative
 // kernel, in one of two forms:
-// - the tile sweep (below, every problem at least 8 points along each axis):
-//   a wavefront takes an 8^3 tile into LDS and solves every cell whose
-//   dependents are solved, until none is left; contributions across a tile
-//   face go through HBM and list the neighbour tile for the next phase;
-// - the level sweep (thin grids): frontiers of points level by level; a point
-//   pushes its contributions to its upwind points with FP64 atomics and
-//   decrements their counters of unsolved dependents, and the point whose
-//   counter reaches zero joins the next frontier.
+// - the tile sweep (below): a wavefront takes an 8^3 tile into LDS and solves
+//   every cell whose dependents are solved, until none is left; contributions
+//   across a tile face go through HBM and list the neighbour tile for the next
+//   phase;
+// - the level sweep (planes and lines, whose tiles would be nearly empty, and
+//   small workspaces): frontiers of points level by level; a point pushes its
+//   contributions to its upwind points with FP64 atomics and decrements their
+//   counters of unsolved dependents, and the point whose counter reaches zero
+//   joins the next frontier.
 #include <math.h>
 #include <string.h>
 
