@@ -311,10 +311,11 @@ typedef struct {
 /* Device workspace for an adjoint batch (0 if invalid): about 36 bytes per
  * grid point of all problems, each axis rounded up to a multiple of 8, or
  * about 29 bytes per point where the rounding up multiplies the points by
- * more than 6 (planes, lines).  A smaller workspace of at least 29 bytes per
- * point (and the problems' descriptors) is accepted for any batch, at a lower
- * speed. */
+ * more than 6 (planes, lines).  fmm_adjoint_workspace_bytes_min() is the
+ * smallest that is accepted for the batch, at a lower speed: about 29 bytes
+ * per point. */
 size_t fmm_adjoint_workspace_bytes(int64_t n_problems, const fmm_adjoint_problem *problems);
+size_t fmm_adjoint_workspace_bytes_min(int64_t n_problems, const fmm_adjoint_problem *problems);
 
 /* dL/dF of every problem of the batch (asynchronous on `stream`; each dL_dF
  * is overwritten, or summed over the problems that share it).  Returns

@@ -587,7 +587,7 @@ static void adj_sizes(int64_t n, const fmm_adjoint_problem *q, std::vector<AdjTi
     *tiles = nt;
 }
 
-size_t fmm_adjoint_workspace_bytes(int64_t n_problems, const fmm_adjoint_problem *problems)
+size_t fmm_adjoint_workspace_bytes_min(int64_t n_problems, const fmm_adjoint_problem *problems)
 {
     if (n_problems <= 0 || n_problems > MAX_PROBLEMS || !problems) return 0;
     for (int64_t i = 0; i < n_problems; i++) {
@@ -597,8 +597,16 @@ size_t fmm_adjoint_workspace_bytes(int64_t n_problems, const fmm_adjoint_problem
     }
     uint64_t total = 0, nt = 0;
     adj_sizes(n_problems, problems, nullptr, &total, &nt);
-    return adj_tiled(n_problems, problems) ? adj_tile_layout(n_problems, nt).total
-                                           : adj_layout(n_problems, total).total;
+    return adj_layout(n_problems, total).total;
+}
+
+size_t fmm_adjoint_workspace_bytes(int64_t n_problems, const fmm_adjoint_problem *problems)
+{
+    const size_t least = fmm_adjoint_workspace_bytes_min(n_problems, problems);
+    if (!least || !adj_tiled(n_problems, problems)) return least;
+    uint64_t total = 0, nt = 0;
+    adj_sizes(n_problems, problems, nullptr, &total, &nt);
+    return adj_tile_layout(n_problems, nt).total;
 }
 
 int fmm_adjoint_batch(int64_t n_problems, const fmm_adjoint_problem *problems, fmm_dtype F_dtype,

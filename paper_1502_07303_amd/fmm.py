@@ -113,8 +113,9 @@ def load_library(path: str = LIB_PATH):
                                    ctypes.c_size_t, P, ctypes.POINTER(FmmOpts), ctypes.POINTER(ctypes.c_float)]
     lib.fmm_tune_batch.restype = ctypes.c_int
     PA = ctypes.POINTER(FmmAdjointProblem)
-    lib.fmm_adjoint_workspace_bytes.argtypes = [i64, PA]
-    lib.fmm_adjoint_workspace_bytes.restype = ctypes.c_size_t
+    for f in (lib.fmm_adjoint_workspace_bytes, lib.fmm_adjoint_workspace_bytes_min):
+        f.argtypes = [i64, PA]
+        f.restype = ctypes.c_size_t
     lib.fmm_adjoint_batch.argtypes = [i64, PA, ctypes.c_int, P, ctypes.c_size_t, P]
     lib.fmm_adjoint_batch.restype = ctypes.c_int
     lib.fmm_adjoint.argtypes = [i64, i64, i64, dbl, P, ctypes.c_int, P, P, P, P, P, ctypes.c_size_t, P]
@@ -489,7 +490,12 @@ class AdjointSolver:
         if nbytes == 0:
             raise FmmError(FMM_EINVAL, "invalid adjoint batch")
         dev = problems[0]["F"].device
-        self.workspace = torch.empty(nbytes + 256, dtype=torch.uint8, device=dev)
+        try:
+            self.workspace = torch.empty(nbytes + 256, dtype=torch.uint8, device=dev)
+        except torch.OutOfMemoryError:
+            # the smallest workspace: the same gradient, more slowly
+            nbytes = int(self.lib.fmm_adjoint_workspace_bytes_min(n, arr))
+            self.workspace = torch.empty(nbytes + 256, dtype=torch.uint8, device=dev)
         off = (-self.workspace.data_ptr()) % 256
         self.ws = self.workspace[off:off + nbytes]
         self.nbytes = nbytes
