@@ -37,13 +37,13 @@ def test_smallest_workspace(shape, n, nbytes):
     assert float((got[0] - got[1]).abs().max()) <= 1e-12 * float(got[0].abs().max())
 
 
-def test_smallest_workspace_where_memory_lacks():
+def test_smallest_workspace_where_memory_lacks(monkeypatch):
     """Where the reported workspace cannot be had, AdjointSolver takes the smallest."""
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
     from paper_1502_07303_amd import fmm
     dev = torch.device("cuda:0")
-    shape = (9, 300, 300)
+    shape = (9, 60, 60)
     F = torch.ones(shape, dtype=torch.float64, device=dev)
     T, st, _ = fmm.solve(F, 1.0, torch.zeros(1, dtype=torch.int64, device=dev),
                          torch.zeros(1, dtype=torch.float64, device=dev), stride=8.0)
@@ -52,18 +52,18 @@ def test_smallest_workspace_where_memory_lacks():
     full = fmm.AdjointSolver(probs)
     full.run()
     full.stats()
-    want, nbytes = probs[0]["dL_dF"].clone(), full.nbytes
-    del full
-    torch.cuda.synchronize()
-    torch.cuda.empty_cache()
-    total = torch.cuda.get_device_properties(dev).total_memory
-    # room for about 40 MB of the 53 MB reported; 23 MB are enough
-    torch.cuda.set_per_process_memory_fraction((torch.cuda.memory_reserved(dev) + (40 << 20)) / total)
-    try:
-        a = fmm.AdjointSolver(probs)
-        assert a.nbytes < nbytes // 2
-        a.run()
-        a.stats()
-    finally:
-        torch.cuda.set_per_process_memory_fraction(1.0)
+    want = probs[0]["dL_dF"].clone()
+    empty = torch.empty
+
+    def limited(size, **kw):
+        if size > full.nbytes // 2:
+            raise torch.OutOfMemoryError("no room")
+        return empty(size, **kw)
+
+    monkeypatch.setattr(fmm.torch, "empty", limited)
+    a = fmm.AdjointSolver(probs)
+    monkeypatch.undo()
+    assert a.nbytes < full.nbytes // 2
+    a.run()
+    a.stats()
     assert float((probs[0]["dL_dF"] - want).abs().max()) <= 1e-12 * float(want.abs().max())
