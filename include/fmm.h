@@ -310,8 +310,9 @@ typedef struct {
 
 /* Device workspace for an adjoint batch (0 if invalid): about 36 bytes per
  * grid point of all problems, each axis rounded up to a multiple of 8, or
- * about 29 bytes per point where the rounding up multiplies the points by
- * more than 6 (planes, lines).  fmm_adjoint_workspace_bytes_min() is the
+ * about 29 bytes per point where a problem has fewer than 8 points along an
+ * axis and the rounding up multiplies the batch's points by more than 3
+ * (planes, lines).  fmm_adjoint_workspace_bytes_min() is the
  * smallest that is accepted for the batch, at a lower speed: about 29 bytes
  * per point. */
 size_t fmm_adjoint_workspace_bytes(int64_t n_problems, const fmm_adjoint_problem *problems);

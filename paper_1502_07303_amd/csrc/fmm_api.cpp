@@ -510,27 +510,31 @@ static bool adj_problem_ok(const fmm_adjoint_problem &q)
     return q.F && q.T && q.status && q.dL_dT && q.dL_dF;
 }
 
-// The tile sweep takes batches whose tiles hold at most ADJT_PAD cells per point.
-// It is the faster of the two at every shape measured, however empty its tiles
-// (ms, tile and level sweep: 7x256x256 3.6 and 11.0, 9x9x9 0.19 and 0.38,
-// 1x1000x1000 6.8 and 20.9, 1x1x5000 7.2 and 34.5), but needs 36 bytes of
-// workspace per cell against the level sweep's 29 per point.  The bound keeps it
-// below 220 bytes per point of the batch: grids with 8 points along each axis
-// and more fill at least a sixth of their tiles, a plane an eighth.  It numbers
-// tiles with 32 bits: larger batches keep the level sweep, too.
-constexpr uint64_t ADJT_PAD = 6;
+// Which batches are sized for the tile sweep.  It is the faster of the two at
+// every shape measured, however empty its tiles (ms, tile and level sweep:
+// 7x256x256 3.6 and 11.0, 9x9x9 0.19 and 0.38, 1x1000x1000 6.8 and 20.9, 1x1x5000
+// 7.2 and 34.5), but needs 36 bytes of workspace per cell against the level
+// sweep's 29 per point, so the line is drawn by memory.  Grids with at least 8
+// points along each axis fill at least a sixth of their tiles (9x9x9; a third
+// from 16 points) and take it.  A batch with a thinner grid takes it while its
+// tiles hold at most ADJT_PAD cells per point, 108 bytes: planes and lines fill
+// an eighth and less, and stay at 29.  It numbers tiles with 32 bits: larger
+// batches keep the level sweep, too.
+constexpr uint64_t ADJT_PAD = 3;
 static bool adj_tiled(int64_t n, const fmm_adjoint_problem *q)
 {
     uint64_t nt = 0, points = 0;
+    bool thin = false;
     for (int64_t i = 0; i < n; i++) {
         int32_t t[3];
         uint64_t k = 0;
         if (!tile_grid(q[i].n0, q[i].n1, q[i].n2, 8, t, &k)) return false;
+        thin |= q[i].n0 < 8 || q[i].n1 < 8 || q[i].n2 < 8;
         points += (uint64_t)(q[i].n0 * q[i].n1 * q[i].n2);
         nt += k;
         if (nt >= 0xFFFFFFF0ull) return false;
     }
-    return 512 * nt <= ADJT_PAD * points;
+    return !thin || 512 * nt <= ADJT_PAD * points;
 }
 
 // The tile sweep's gather reads F while it writes dL_dF (the level sweep has read

@@ -1,5 +1,5 @@
-"""Which sweep a batch is sized for: the tile sweep's where its 8^3 tiles hold at
-most six cells per point of the batch, whatever the thickness of a single grid.
+"""Which sweep a batch is sized for: the tile sweep's where every grid has 8 points
+along each axis, or the 8^3 tiles hold at most three cells per point of the batch.
 Either way dL/dF and the dependency levels are those of the oracle's upwind system
 solved by back substitution; bar 1e-12 of the largest gradient, the suite's for the
 adjoint on given T."""
@@ -13,10 +13,10 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("shapes,tiled", [
-    ([(7, 24, 17)], True), ([(2, 24, 24)], True), ([(3, 11, 11)], True), ([(3, 10, 10)], False), ([(9, 9, 9)], True),
-    ([(1, 16, 16)], False), ([(1, 1, 40)], False), ([(6, 6, 6)], True), ([(4, 4, 4)], False), ([(16, 17, 16), (1, 9, 20)], True),
-    ([(1, 9, 20), (9, 8, 11), (1, 1, 9)], False), ([(1, 9, 20), (9, 8, 12), (1, 1, 9)], True),
-    ([(1, 9, 9), (1, 9, 9), (8, 8, 8)], False), ([(1, 9, 9), (8, 8, 8)], True), ([(1, 9, 9)] * 5 + [(5, 5, 5)], False)])
+    ([(7, 24, 17)], True), ([(3, 16, 16)], True), ([(2, 16, 16)], False), ([(7, 10, 10)], True), ([(7, 9, 9)], False),
+    ([(3, 11, 11)], False), ([(9, 9, 9)], True), ([(1, 16, 16)], False), ([(1, 1, 40)], False), ([(6, 6, 6)], True),
+    ([(4, 4, 4)], False), ([(16, 17, 16), (1, 9, 20)], True), ([(1, 9, 20), (9, 8, 12), (1, 1, 9)], False),
+    ([(8, 8, 8), (1, 8, 8), (8, 8, 8)], True), ([(1, 9, 9), (8, 8, 8)], False), ([(1, 9, 9)] * 5 + [(5, 5, 5)], False)])
 @pytest.mark.parametrize("dtype,scale", [(torch.float64, None), (torch.float32, (1.0, 1.7, 0.6))])
 def test_route(oracle_mod, shapes, tiled, dtype, scale):
     if not torch.cuda.is_available():
@@ -35,7 +35,8 @@ def test_route(oracle_mod, shapes, tiled, dtype, scale):
                       "dL_dF": torch.empty(shape, dtype=torch.float64, device=dev), "axis_scale": scale})
     a = fmm.AdjointSolver(probs)
     cells = sum(512 * int(np.prod([-(-n // 8) for n in s])) for s in shapes)
-    assert tiled == (cells <= 6 * sum(int(np.prod(s)) for s in shapes))
+    thin = min(min(s) for s in shapes) < 8
+    assert tiled == (not thin or cells <= 3 * sum(int(np.prod(s)) for s in shapes))
     assert (a.nbytes >= 36 * cells) == tiled
     for _ in range(2):
         a.run()
