@@ -151,9 +151,9 @@ __device__ __forceinline__ double godunov_sel(double x, double y, double z, doub
 // then differ by about (u - a)^2 / (4 r), which exceeds a few ulps of the values
 // once |r^2 - sum| > r^2 2^-22 sqrt(a1 / r), and t bounds twice that without a
 // root.  Closer calls, and r^2 near the ends of the exponent range (r = +inf
-// too), take godunov_sel(): bitwise the same result everywhere (checked on the
-// host on 4e8 triples, most of them around the decisions).  NaN sums, from
-// absent values, compare false and leave the first root.
+// too), take godunov_sel(): bitwise the same result everywhere (the tests compare
+// random triples, both decisions, ties and the ends of the range).  NaN sums,
+// from absent values, compare false and leave the first root.
 __device__ __forceinline__ double godunov(double x, double y, double z, double r)
 {
     const double lo = fmin(x, y), hi = fmax(x, y);
@@ -193,8 +193,8 @@ __device__ __forceinline__ double godunov(double x, double y, double z, double r
 // with the same causality rule and minimum.  With unit scales every
 // operation is the one of godunov_sel().  Both roots are formed without a
 // branch, with the short root and quotient and the weights of the axes instead
-// of those of the sorted scales: the same operations, so the same bits (8e8
-// random arguments, scales and r over all exponents among them).  A march is
+// of those of the sorted scales: the same operations, so the same bits (the tests
+// compare ties, both decisions and wide ranges of values, r and scales).  A march is
 // bound by its instructions, and this took five divisions and two roots of the
 // library: 101x87x118, 3 spacings, 6.49 -> 5.81 ms.
 __device__ __forceinline__ double godunov_w_sel(double x, double y, double z, double sx, double sy, double sz,

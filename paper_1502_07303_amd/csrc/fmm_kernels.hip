@@ -633,8 +633,8 @@ __device__ __forceinline__ int relax(KParams P, TileLds<E, FT, G> &L, double h, 
                 const double a = TWO ? fabs(nv) : nv;
                 if (src) {
                     // mark the downwind interior neighbours.  Seeds and
-                    // impassable cells may be marked too: their LDS speed is
-                    // 0, so their solve gives +inf and changes nothing.
+                    // impassable cells may be marked too: their solve gives
+                    // NaN or +inf (cell_r()), which changes nothing.
                     const int i0 = p >> (2 * Gm::LOG), i1 = (p >> Gm::LOG) & (E - 1), i2 = p & (E - 1);
                     if constexpr (TileLds<E, FT, G>::BITS) {
                         mark_cand(L, i0 > 0 && na[0] > a, p - E * E);
