@@ -115,7 +115,8 @@ __device__ __forceinline__ double adj_term(double h, double f, double lambda, in
     const double mf = __builtin_amdgcn_frexp_mant(f);
     const double q = quick_div(__builtin_amdgcn_frexp_mant(h), mf);  // h / F
     const int eq = __builtin_amdgcn_frexp_exp(h) - __builtin_amdgcn_frexp_exp(f);
-    const double m = fast_div(__builtin_amdgcn_frexp_mant(lambda) * q * q, mf);  // lambda may be infinite or NaN
+    double m = quick_div(__builtin_amdgcn_frexp_mant(lambda) * q * q, mf);
+    m = __builtin_amdgcn_class(lambda, 0x1 | 0x2 | 0x4 | 0x200) ? lambda : m;  // NaN and infinities
     return __builtin_amdgcn_ldexp(-m, __builtin_amdgcn_frexp_exp(lambda) + e + 2 * eq - __builtin_amdgcn_frexp_exp(f));
 }
 
