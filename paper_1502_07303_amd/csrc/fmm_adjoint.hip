@@ -346,8 +346,8 @@ static int adj_cus()
 // scattered atomics per point through memory.  A tile runs through many levels
 // between two barriers, with its atomics in LDS: 400 phases instead of 2481
 // levels, and only contributions across tile faces go through memory.  256^3,
-// 16 shots: 150.4 ms with the level sweep, 42.9 ms with this one (setup 7.4 ms at
-// 3.7 TB/s, sweep 34.3 ms, gather 0.9 ms at 4.8 TB/s).
+// 16 shots: 150.4 ms with the level sweep, 43.1 ms with this one (setup 7.4 ms at
+// 3.7 TB/s, sweep 34.7 ms, gather 0.93 ms at 4.6 TB/s).
 //
 // What bounds it.  A tile is activated 7.5 times (contributions arrive over
 // several phases) and solves its cells in rounds of about 7, the width of its
