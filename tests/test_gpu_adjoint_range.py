@@ -76,3 +76,34 @@ def test_adjoint_range(oracle_mod, level, k, spread, gk, scale):
     assert np.all(got[ref == 0] == 0)
     zero = np.abs(ref) < LD(2) ** -1080
     assert np.all(np.abs(got[zero]) < 2.0 ** -1060)
+
+
+@pytest.mark.parametrize("level", [False, True])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float64])
+def test_adjoint_infinite_speeds(oracle_mod, level, dtype):
+    """Infinite speeds beside the seed and elsewhere, by the library's own forward
+    solve: zero gradient there, the reference's everywhere else."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1502_07303_amd import fmm
+    dev = torch.device("cuda:0")
+    shape, h = (11, 9, 17), 2.0 ** -4
+    rng = np.random.default_rng(12)
+    F = rng.uniform(0.5, 2.0, shape)
+    at = np.concatenate([[5 * 153 + 4 * 17 + 4, 5 * 153 + 5 * 17 + 3, 4 * 153 + 4 * 17 + 3], rng.choice(F.size, 60, False)])
+    F.reshape(-1)[at] = np.inf
+    F.reshape(-1)[5 * 153 + 4 * 17 + 3] = 1.0
+    Fd = torch.from_numpy(F).to(dtype).to(dev)
+    T, st, _ = fmm.solve(Fd, h, torch.tensor([5 * 153 + 4 * 17 + 3], device=dev), torch.zeros(1, dtype=torch.float64, device=dev))
+    g = rng.uniform(0.5, 1.0, shape)
+    F = Fd.cpu().numpy().astype(np.float64)
+    ref, acc = reference(F, h, T.cpu().numpy(), st.cpu().numpy(), g)
+    gF = torch.empty(shape, dtype=torch.float64, device=dev)
+    a = fmm.AdjointSolver([{"F": Fd, "h": h, "T": T, "status": st, "dL_dT": torch.from_numpy(g).to(dev), "dL_dF": gF}])
+    if level:
+        a.nbytes -= 1
+    a.run()
+    a.stats()
+    got = gF.cpu().numpy().reshape(-1)
+    assert np.all(got[np.isinf(F.reshape(-1))] == 0.0)
+    assert np.all(np.abs(got - ref) <= 1e-12 * np.abs(ref))
