@@ -350,7 +350,7 @@ static int adj_cus()
 // between two barriers, with its atomics in LDS: 400 phases instead of 2481
 // levels, and only contributions across tile faces go through memory.  256^3,
 // 16 shots: 150.4 ms with the level sweep, 43.1 ms with this one (setup 7.4 ms at
-// 3.7 TB/s, sweep 34.7 ms, gather 0.93 ms at 4.6 TB/s).
+// 3.7 TB/s, sweep 34.7 ms, gather 0.95 ms at 4.6 TB/s).
 //
 // What bounds it.  A tile is activated 7.5 times (contributions arrive over
 // several phases) and solves its cells in rounds of about 7, the width of its

@@ -2225,9 +2225,9 @@ static hipError_t launch_driver_t(const Params &P, hipStream_t s, uint32_t *nwg_
     // One full occupancy wave, but no more workgroups than the tiles can use:
     // a phase's items go to the workgroups in turn, so a workgroup per eight
     // tiles leaves every tile a wavefront of its own with few to a CU, and the
-    // device barrier gets cheaper (256 workgroups 7.4 to 10.8 us from box to
-    // box, 64 2.4 us, 16 1.0 us).  64^3 shells 8.4 -> 7.9 ms, 24x20x28 1.00 -> 0.85 ms; one workgroup
-    // per 4 or 12 tiles: 8.2 and 7.9 ms, 0.85 and 0.86 ms.
+    // device barrier gets cheaper (256 workgroups 7.4 to 10.8 us from machine to
+    // machine, 64 2.4 us, 16 1.0 us).  64^3 shells 8.4 -> 7.9 ms, 24x20x28 1.00 ->
+    // 0.85 ms; one workgroup per 4 or 12 tiles: 8.2 and 7.9 ms, 0.85 and 0.86 ms.
     const unsigned per_wg = G == 64 ? 8u : 1u;
     const unsigned grid = std::min((unsigned)(occ * num_cus()), (P.ntiles + per_wg - 1) / per_wg);
     Params Pc = P;
